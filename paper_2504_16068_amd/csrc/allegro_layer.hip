@@ -18,8 +18,9 @@
 //                       persistent workgroups with register accumulators,
 //                       one partial per workgroup, then colsum_kernel
 //   mix_kernel          per-irrep channel mixing V' = Mix_c T_c (forward) or
-//                       dT = Mix_c^T dV' (backward); each wave keeps its 16
-//                       output channels' rows of every Mix_c in registers
+//                       dT = Mix_c^T dV' (backward), in fp32 through split
+//                       operands on the bf16 matrix cores; each wave keeps
+//                       rows of its irreps' Mix_c in registers
 //   mix_wgrad_kernel    dMix_c = sum over edges and components of dV'_c T_c^T
 //   colsum_kernel       fixed-order sum of the workgroups' partials
 //
@@ -46,6 +47,11 @@ using allegro_internal::fail;
 constexpr int kWave = 64;
 constexpr int kThreads = 256;  // four waves per workgroup
 constexpr int kU = 64;         // channels supported by the layer
+constexpr int kBufferNonTemporal = 2;  // buffer access policy bit (streamed once)
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x4 mfma_16x16x4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -60,10 +66,11 @@ __device__ __forceinline__ float silu_grad(float a) {
 
 // The x irreps of a plan: for l = 0..lmax, (l, natural parity) then, with
 // full parity, (l, the other parity); sizes 2l + 1, concatenated.
-template <int LMAX, bool FULL>
+template <int LMAX_, bool FULL>
 struct XIrreps {
-  static constexpr int NX = FULL ? 2 * (LMAX + 1) : LMAX + 1;
-  static constexpr int D1 = FULL ? 2 * (LMAX + 1) * (LMAX + 1) : (LMAX + 1) * (LMAX + 1);
+  static constexpr int LMAX = LMAX_;
+  static constexpr int NX = FULL ? 2 * (LMAX_ + 1) : LMAX_ + 1;
+  static constexpr int D1 = FULL ? 2 * (LMAX_ + 1) * (LMAX_ + 1) : (LMAX_ + 1) * (LMAX_ + 1);
   static constexpr int dim(int c) { return 2 * (FULL ? c / 2 : c) + 1; }
   static constexpr int off(int c) { return c == 0 ? 0 : off(c - 1) + dim(c - 1); }
 };
@@ -79,6 +86,7 @@ struct RowGemmArgs {
   int b_rs, b_cs;
   const float *d;        // addend (kEpiAdd, kEpiSplitAdd) or pre-activation (kEpiSiluGrad)
   float *c, *c2;         // output; kEpiSplitAdd: columns < N1 to c, the rest to c2
+  int *ticket;           // set to zero for the mixing kernel launched after this one (may be null)
 };
 
 constexpr int kRowTile = 64;  // rows per workgroup tile
@@ -157,6 +165,7 @@ __global__ __launch_bounds__(kThreads) void row_gemm_kernel(RowGemmArgs g) {
   __shared__ float4 xs4[LDSF / 4];
   float *xs = reinterpret_cast<float *>(xs4);
   const int tid = threadIdx.x, wave = tid / kWave, l = tid % kWave;
+  if (g.ticket && blockIdx.x == 0 && tid == 0) *g.ticket = 0;
   // step s pairs k = 4 s + l / 16 in both operands
   float bf[NJ][K / 4];
 #pragma unroll
@@ -357,204 +366,436 @@ __device__ __forceinline__ void component_column(int k, int ne_tile, int &col0, 
   dim = d;
 }
 
-constexpr int kMixEdges = 8;       // edges per tile
-// Column stride (floats): a multiple of 4, so a lane reads its 16 B operands
-// of a step block as four 16-byte LDS loads, and 68 = 4 (mod 64), so the 16
-// columns of a tile start in distinct bank quads.
-constexpr int kMixCS = kU + 4;
-constexpr int kMixThreads = 512;   // four compute waves, then four memory waves
+// fp32 products on the bf16 matrix cores.  x = h + m + l with h = bf16(x),
+// m = bf16(x - h), l = x - h - m: 8 significant bits each, rounded to nearest,
+// so the three hold all 24 bits of x exactly (both subtractions are exact).
+// Of the nine products of two split operands the six of weight 2^-16 and more
+// are summed (in fp32, by the matrix core), the small ones first; the three
+// dropped are below 2^-26 of the product, a quarter of the rounding of one
+// fp32 product.  The matrix core takes bf16 subnormals as zero, so both
+// operands are scaled by kSplitScale first: the smallest part of any fp32
+// value, 2^-149, is then a normal number.  The sum comes back through
+// kSplitUnscale; what overflows for the scale (or is infinite to begin with)
+// leaves a sum that is not finite, and the caller redoes it in fp32.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
-// Per-irrep channel mixing, software-pipelined over two LDS tile buffers.
-// Waves 0-3 (compute) hold rows 16w .. 16w+15 of every Mix_c (Mix_c^T for the
-// backward) in registers and run the matrix-core products on one buffer,
-// while waves 4-7 (memory) store the previous tile's results from the other
-// buffer and refill it with the next tile.  Per tile the two roles meet at
-// two workgroup barriers: after the first the compute waves write their
-// results into their buffer in place, after the second the buffers swap.
-// Both roles run the same tile sequence, so their barrier counts match.
-template <class X>
-struct MixTile {
-  static constexpr int U = kU, D1 = X::D1, NX = X::NX, NE = kMixEdges, CS = kMixCS;
-  static constexpr int COLS = NE * D1;
-  static constexpr int BUF = (COLS + 16) * CS;  // +16 columns: the last irrep's padded column tile
-  static constexpr int F4 = NE * U * D1 / 4;    // float4 per full tile
-  static constexpr int PER = (F4 + 255) / 256;  // float4 per memory thread
-  static constexpr int ncols(int c) { return NE * X::dim(c); }
-  static constexpr int nct(int c) { return (ncols(c) + 15) / 16; }
-  static constexpr int ct_off(int c) { return c == 0 ? 0 : ct_off(c - 1) + nct(c - 1); }
-  static constexpr int NCT = ct_off(NX);
-  static_assert((U * D1) % 4 == 0, "edge rows must be whole float4");
-  static_assert(CS % 4 == 0, "operand blocks are read as 16-byte LDS loads");
+struct Split8 {
+  bf16x8 h, m, l;
 };
 
-template <class X, bool BWD>
-__device__ __forceinline__ void mix_compute_role(int64_t E, int64_t n_tiles, const float *__restrict__ mix,
-                                                 const float *__restrict__ ds, float *__restrict__ s_out,
-                                                 float *lds) {
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 h, m, l;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x2 v = {kSplitScale * x[2 * i], kSplitScale * x[2 * i + 1]};
+    const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    const f32x2 r = {v.x - __builtin_bit_cast(float, hb << 16), v.y - __builtin_bit_cast(float, hb & 0xffff0000u)};
+    const uint32_t mb = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+    const f32x2 q = {r.x - __builtin_bit_cast(float, mb << 16), r.y - __builtin_bit_cast(float, mb & 0xffff0000u)};
+    h[i] = hb;
+    m[i] = mb;
+    l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, bf16x2));
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+__device__ __forceinline__ f32x4 mfma_split(const Split8 &a, const Split8 &b, f32x4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b.h, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.l, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.m, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.h, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.m, c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, c, 0, 0, 0);
+}
+
+// Column stride (floats): 68 = 4 (mod 64), so the 16-byte accesses of one
+// channel quad in 16 consecutive columns start in distinct bank quads.
+constexpr int kMixCS = kU + 4;
+constexpr int kMixComputeWaves = 8, kMixMemoryWaves = 4;
+constexpr int kMixThreads = kWave * (kMixComputeWaves + kMixMemoryWaves);
+
+// Channel at position p of a column: positions 4 u .. 4 u + 3 hold channels u,
+// u + 16, u + 32 and u + 48, so that a memory thread moves four channels of a
+// component as one 16-byte LDS access while a wave's global accesses cover
+// consecutive rows.
+__device__ __forceinline__ constexpr int mix_channel(int p) { return 16 * (p & 3) + (p >> 2); }
+
+// Per-irrep channel mixing, software-pipelined over two LDS tile buffers.
+// Waves 0-7 (compute) run the matrix-core products on one buffer while waves
+// 8-11 (memory) store the previous tile's results from the other buffer and
+// refill it with the next tile.  Per tile the two roles meet at two workgroup
+// barriers: after the first the compute waves write their results into their
+// buffer in place, after the second the buffers swap.  Both roles run the same
+// tile sequence, so their barrier counts match.
+//
+// The tiles of a workgroup: the first three by its index, the rest in the order
+// in which the workgroups of the whole device come to ask (ticket, zero before
+// the launch), so that at any time they work on neighbouring tiles.  With a
+// fixed stride per workgroup they drift apart (in a copy kernel with this tile
+// size by up to 22 tiles), and HBM serves the widely spread streams at 5.4-5.7
+// TB/s where the compact ones reach 6.8.  The first compute wave takes tile
+// p + 3 during period p and leaves it at order[(p + 3) % 4] before B2.
+//
+// A compute wave owns the irreps of one pair of orders (l = 0 with 3, 1 with 2)
+// at one parity, 8 of lmax 3's 32 components each, and 16 RT of the output
+// channels; it holds its rows of their Mix matrices in registers, split into
+// three bf16 parts (mfma_split).  A column is then read by 4 / RT waves
+// instead of by all, which pays for splitting it on the way (5 vector
+// operations a value), and the fp32 matrix instructions that set this kernel's
+// pace (20 column tiles x 16 steps x 32 cycles per 8 edges and SIMD at lmax 3)
+// become 5 x 24 x 2 x 16.  Bound now by HBM: with the products skipped the
+// kernel takes as long.  Measured at lmax 3, full parity, 523,599 edges (8.6
+// GB): fp32 products in fixed order 2.04 ms; these products 1.65 ms; tiles in
+// order of arrival 1.37 ms (6.3 TB/s).  lmax 2, 206,624 edges: 478, 357 (14
+// edges a tile instead of 8), 305 us.
+template <class X>
+struct MixTile {
+  static constexpr int U = kU, D1 = X::D1, NX = X::NX, CS = kMixCS;
+  // Edges per tile: about the 64 KB a compute unit must have in flight (at lmax 2
+  // 8 edges, 36 KB, left it short of loads), and 16 where that fills the column tiles.
+  static constexpr int NE = D1 == 32 ? 8 : D1 == 18 ? 14 : D1 >= 9 ? 16 : 32;
+  static constexpr int COLS = NE * D1;
+  static constexpr int BUF = (COLS + 16) * CS;  // +16 columns: the last irrep's padded column tile
+  static constexpr int VW = D1 % 4 == 0 ? 4 : D1 % 2 == 0 ? 2 : 1;  // components per global access
+  static constexpr int CH = D1 / VW;                                // accesses per row
+  // memory task: VW components of the four channels u, u + 16, u + 32, u + 48 of an edge
+  static constexpr int TASKS = NE * 16 * CH, PER = (TASKS + kWave * kMixMemoryWaves - 1) / (kWave * kMixMemoryWaves);
+  static constexpr int PARITIES = X::NX > X::LMAX + 1 ? 2 : 1;
+  static constexpr int PAIRS = X::LMAX == 1 ? 1 : 2;
+  // row splits: the compute waves over the irrep groups, at least 16 channels each
+  static constexpr int RS = PARITIES * PAIRS == 4 ? 2 : 4, RT = 4 / RS;
+  static constexpr int BUSY = PARITIES * PAIRS * RS;
+  // the two orders of pair i (-1: none)
+  static constexpr int la(int i) { return X::LMAX == 2 && i == 1 ? 2 : i; }
+  static constexpr int lb(int i) { return X::LMAX == 3 ? 3 - i : X::LMAX == 2 && i == 1 ? -1 : 1; }
+  static constexpr int nct(int l) { return l < 0 ? 0 : (NE * (2 * l + 1) + 15) / 16; }  // column tiles
+  static_assert(BUSY <= kMixComputeWaves, "compute waves");
+};
+
+template <class X, bool BWD, int LA, int LB>
+__device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_tiles, const float *__restrict__ mix,
+                                                  float *lds, int *order, int *__restrict__ ticket) {
   using M = MixTile<X>;
-  constexpr int U = M::U, CS = M::CS, NE = M::NE;
-  const int tid = threadIdx.x, w = tid / kWave, l = tid % kWave;
-  // A operands: row 16 w + l % 16 of Mix_c (or of Mix_c^T), columns 16 (l / 16) + s
-  float A[M::NX][16];
-  static_for<0, M::NX>([&](auto ic) {
-    constexpr int c = decltype(ic)::value;
+  constexpr int U = M::U, CS = M::CS, NE = M::NE, RT = M::RT, NS = LB < 0 ? 1 : 2;
+  constexpr int TA = M::nct(LA), NT = TA + M::nct(LB);  // column tiles of the first irrep, of both
+  int l = threadIdx.x % kWave;
+  asm volatile("" : "+v"(l));  // nothing derived from it is shared, and held, across the pairs' code
+  const int g = l / 16, q = l % 16;
+  // The irreps, and the lane's LDS offsets in a buffer of its reads (rd) and
+  // writes (wr) in their first column tile; opaque, so that the tiles' addresses
+  // are immediate offsets from these and not a register each.
+  const int cs[2] = {M::PARITIES * LA + par, M::PARITIES * (LB < 0 ? 0 : LB) + par};
+  int rd[2], wr[2];
 #pragma unroll
-    for (int s = 0; s < 16; ++s)
-      A[c][s] = BWD ? mix[(c * U + 16 * (l / 16) + s) * U + 16 * w + l % 16]
-                    : mix[(c * U + 16 * w + l % 16) * U + 16 * (l / 16) + s];
-  });
-  lds_sync<8>();  // the first tile is in buffer 0
-  int p = 0;
-  for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x, ++p) {
+  for (int s = 0; s < NS; ++s) {
+    constexpr int lo[2] = {LA, LB};
+    // the components before irrep (l, par): l^2 of each parity, then the other parity of l
+    const int col = NE * (M::PARITIES * lo[s] * lo[s] + par * (2 * lo[s] + 1)) + q;
+    rd[s] = col * CS + 16 * g;
+    wr[s] = col * CS + 16 * RT * rs + 4 * g;
+    asm volatile("" : "+v"(rd[s]), "+v"(wr[s]));
+  }
+  // element (row position pr, reduction position pk) of Mix_c, transposed for the backward
+  auto elem = [&](int c, int pr, int pk) {
+    const int r = mix_channel(pr), k = mix_channel(pk);
+    return BWD ? mix[(c * U + k) * U + r] : mix[(c * U + r) * U + k];
+  };
+  // step ks of lane group g covers positions 16 g + 8 ks .. + 7
+  Split8 A[NS][RT][2];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = elem(cs[s], 16 * (RT * rs + rt) + q, 16 * g + 8 * ks + j);
+        A[s][rt][ks] = split8(x);
+      }
+  lds_sync<12>();  // the first tile is in buffer 0
+  const bool taker = LA == 0 && par == 0 && rs == 0;
+  for (int p = 0; __builtin_amdgcn_readfirstlane(order[p & 3]) < n_tiles; ++p) {
+    int tile = 0;
+    if (taker && l == 0) tile = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     float *b = lds + (p & 1) * M::BUF;
-    const int64_t e0 = t * NE;
-    const int ne = int(E - e0 < NE ? E - e0 : NE);
-    // backward: the lane's ds terms for the 0e columns (column q = edge q), loaded
-    // now so that their latency hides under the products
-    float dsv[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (BWD) {
-      if (l % 16 < ne) {
+    f32x4 acc[NT][RT];
+    float bad = 0.f;  // becomes NaN if a product is not finite
+    static_for<0, NT>([&](auto it) {
+      constexpr int i = decltype(it)::value, s = i < TA ? 0 : 1, ct = i < TA ? i : i - TA;
+      constexpr int nq = NE * (2 * (s == 0 ? LA : LB) + 1);
+      const float4 *bp = reinterpret_cast<const float4 *>(b + rd[s] + 16 * ct * CS);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dsv[r] = ds[(e0 + l % 16) * U + 16 * w + 4 * (l / 16) + r];
+      for (int rt = 0; rt < RT; ++rt) acc[i][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const float4 u = bp[2 * ks], v = bp[2 * ks + 1];
+        const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+        const Split8 B = split8(x);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[i][rt] = mfma_split(A[s][rt][ks], B, acc[i][rt]);
       }
-    }
-    f32x4 acc[M::NCT];
-    static_for<0, M::NX>([&](auto ic) {
-      constexpr int c = decltype(ic)::value, base = NE * X::off(c);
+      if (16 * ct + q < nq) {
 #pragma unroll
-      for (int ct = 0; ct < M::nct(c); ++ct) {
-        // the lane's 16 operands (channels 16 (l / 16) .. + 15 of column 16 ct + l % 16) are contiguous
-        const float4 *bp = reinterpret_cast<const float4 *>(b + (base + 16 * ct + l % 16) * CS + 16 * (l / 16));
-        float bv[16];
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float4 x = bp[j];
-          bv[4 * j] = x.x; bv[4 * j + 1] = x.y; bv[4 * j + 2] = x.z; bv[4 * j + 3] = x.w;
+          for (int r = 0; r < 4; ++r) bad = __builtin_fmaf(acc[i][rt][r], 0.f, bad);
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][rt][r] *= kSplitUnscale;
+    });
+    if (__any(bad != bad)) {
+      // An infinity (or a value or sum too large for the scale) has left inf - inf:
+      // redo the wave's products in fp32, which carries it through as it is.  (The
+      // opaque lane index keeps these addresses out of the loop's registers.)
+      int lane = l;
+      asm volatile("" : "+v"(lane));
+      const int go = lane / 16, qo = lane % 16;
+      static_for<0, NT>([&](auto it) {
+        constexpr int i = decltype(it)::value, s = i < TA ? 0 : 1, ct = i < TA ? i : i - TA;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int k = 0; k < 16; ++k)
+            a = mfma_16x16x4(elem(cs[s], 16 * (RT * rs + rt) + qo, 16 * go + k),
+                             b[rd[s] + 16 * ct * CS + k], a);
+          acc[i][rt] = a;
         }
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+      });
+    }
+    lds_sync<12>();  // B1: every compute wave has read the tile
+    static_for<0, NT>([&](auto it) {
+      constexpr int i = decltype(it)::value, s = i < TA ? 0 : 1, ct = i < TA ? i : i - TA;
+      constexpr int nq = NE * (2 * (s == 0 ? LA : LB) + 1);
+      if (16 * ct + q < nq) {
 #pragma unroll
-        for (int s = 0; s < 16; ++s) a = mfma_16x16x4(A[c][s], bv[s], a);
-        acc[M::ct_off(c) + ct] = a;
+        for (int rt = 0; rt < RT; ++rt) {
+          f32x4 v = acc[i][rt];
+          // the 0e irrep also has the gradient of s: [edge][position] behind the tile buffers
+          if (BWD && LA == 0 && s == 0 && par == 0)
+            v += *reinterpret_cast<const f32x4 *>(lds + 2 * M::BUF + (16 * ct + q) * U + 16 * (RT * rs + rt) + 4 * g);
+          *reinterpret_cast<f32x4 *>(b + wr[s] + 16 * ct * CS + 16 * rt) = v;
+        }
       }
     });
-    if constexpr (!BWD) {
-      // s[e][u] = T[e][u][0]: irrep 0 (0e) has one component, so its column is e
-      for (int i = tid; i < ne * U; i += 256) s_out[(e0 + i / U) * U + i % U] = b[(i / U) * CS + i % U];
-    }
-    lds_sync<8>();  // B1: every compute wave has read the tile
-    static_for<0, M::NX>([&](auto ic) {
-      constexpr int c = decltype(ic)::value, base = NE * X::off(c), nq = M::ncols(c);
-#pragma unroll
-      for (int ct = 0; ct < M::nct(c); ++ct) {
-        const int q = 16 * ct + l % 16;
-        if (q >= nq) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int uo = 16 * w + 4 * (l / 16) + r;
-          float val = acc[M::ct_off(c) + ct][r];
-          if constexpr (BWD && c == 0) val += dsv[r];  // zero for columns past the tile's edges
-          b[(base + q) * CS + uo] = val;
-        }
-      }
-    });
-    lds_sync<8>();  // B2: results are in the buffer
+    if (taker && l == 0) order[(p + 3) & 3] = 3 * int(gridDim.x) + tile;
+    lds_sync<12>();  // B2: results are in the buffer
   }
 }
 
-template <class X>
-__device__ __forceinline__ void mix_memory_role(int64_t E, int64_t n_tiles, const float *__restrict__ src,
-                                                float *__restrict__ dst, float *lds) {
+template <class X, bool BWD>
+__device__ __forceinline__ void mix_compute_role(int64_t n_tiles, const float *__restrict__ mix, float *lds,
+                                                 int *order, int *__restrict__ ticket) {
   using M = MixTile<X>;
-  constexpr int U = M::U, D1 = M::D1, NE = M::NE, PER = M::PER, F4 = M::F4;
-  const int mt = int(threadIdx.x) - 256;
-  // The thread's float4 of a tile: fi(i) = f0 + 16 i.  Each group of 16 lanes
-  // covers 256 contiguous bytes per access (coalesced), and a thread's float4
-  // lie 256 B apart, within the reach of one base address and immediate
-  // offsets (4 KB apart, as with fi(i) = mt + 256 i, measured 4% slower).
-  const int f0 = (mt / 16) * (16 * PER) + mt % 16;
-  auto fi = [&](int i) { return f0 + 16 * i; };
-  // LDS offset (within a buffer) of each of the thread's elements: component k
-  // of channel u of edge e sits in column NE off(c) + e dim(c) + m, row u
-  int addr[PER][4];
-#pragma unroll
-  for (int i = 0; i < PER; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = 4 * fi(i) + q;
-      int a = 0;
-      if (idx < 4 * F4) {
-        const int e = idx / (U * D1), rem = idx % (U * D1), u = rem / D1, k = rem % D1;
-        int col0, dim;
-        component_column<X>(k, NE, col0, dim);
-        a = (col0 + e * dim) * M::CS + u;
-      }
-      addr[i][q] = a;
+  // wave-uniform: row split, parity, pair of orders
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  const int rs = w % M::RS, par = (w / M::RS) % M::PARITIES, pair = w / (M::RS * M::PARITIES);
+  if (w >= M::BUSY) {  // no irreps left for this wave: it only keeps the barrier count
+    lds_sync<12>();
+    for (int p = 0; __builtin_amdgcn_readfirstlane(order[p & 3]) < n_tiles; ++p) {
+      lds_sync<12>();
+      lds_sync<12>();
     }
-  auto count = [&](int64_t t) { return int(E - t * NE < NE ? E - t * NE : NE) * (U * D1 / 4); };
-  auto load = [&](int64_t t, float4 (&v)[PER]) {
-    const int nf4 = count(t);
-    const float4 *s4 = reinterpret_cast<const float4 *>(src + t * NE * U * D1);
+  } else if (pair == 0) {
+    mix_compute_waves<X, BWD, M::la(0), M::lb(0)>(par, rs, n_tiles, mix, lds, order, ticket);
+  } else if constexpr (M::PAIRS > 1) {
+    mix_compute_waves<X, BWD, M::la(1), M::lb(1)>(par, rs, n_tiles, mix, lds, order, ticket);
+  }
+}
+
+// VW consecutive floats by buffer access: past the descriptor's range loads
+// give zeros and stores are dropped.
+template <int VW>
+using FloatVec = float __attribute__((ext_vector_type(VW)));
+
+template <int VW>
+__device__ __forceinline__ FloatVec<VW> buffer_load_f(__amdgpu_buffer_rsrc_t r, int off) {
+  using V = FloatVec<VW>;
+  if constexpr (VW == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kBufferNonTemporal));
+  else if constexpr (VW == 2) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kBufferNonTemporal));
+  else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kBufferNonTemporal));
+}
+
+template <int VW>
+__device__ __forceinline__ void buffer_store_f(__amdgpu_buffer_rsrc_t r, int off, FloatVec<VW> v) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  if constexpr (VW == 4)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kBufferNonTemporal);
+  else if constexpr (VW == 2)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, kBufferNonTemporal);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, kBufferNonTemporal);
+}
+
+template <class X, bool BWD>
+__device__ __forceinline__ void mix_memory_role(int64_t E, int64_t n_tiles, const float *__restrict__ src,
+                                                const float *__restrict__ ds, float *__restrict__ dst,
+                                                float *__restrict__ s_out, float *lds, const int *order) {
+  using M = MixTile<X>;
+  constexpr int U = M::U, D1 = M::D1, NE = M::NE, PER = M::PER, VW = M::VW, CH = M::CH;
+  constexpr int THREADS = kWave * kMixMemoryWaves;
+  const int mt = int(threadIdx.x) - kWave * kMixComputeWaves;
+  // Task j of the thread: components VW b .. of channels u + 16 i (i = 0..3) of
+  // edge e, task index (e 16 + u) CH + b = mt + 256 j: for one i consecutive
+  // lanes cover consecutive bytes.  In LDS the four channels of a component
+  // are one 16-byte access at addr.
+  int off[PER], addr[PER][VW];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int f = fi(i);
-      v[i] = f < nf4 ? load_stream(s4 + f) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int j = 0; j < PER; ++j) {
+    const int task = mt + THREADS * j, bch = task % CH, u = (task / CH) % 16, e = task / (16 * CH);
+    off[j] = 4 * ((e * U + u) * D1 + VW * bch);  // bytes within the tile; e >= NE lies past its range
+#pragma unroll
+    for (int q = 0; q < VW; ++q) {
+      int col0, dim;
+      component_column<X>(VW * bch + q, NE, col0, dim);
+      addr[j][q] = task < M::TASKS ? (col0 + e * dim) * M::CS + 4 * u : 0;
+    }
+  }
+  // tile t of an [E][U][width] tensor, as far as it has edges; empty for no tile
+  auto rsrc = [&](const float *base, int width, int64_t t) {
+    const bool valid = t >= 0 && t < n_tiles;
+    const int64_t e0 = valid ? t * NE : 0;
+    const int ne = valid ? int(E - e0 < NE ? E - e0 : NE) : 0;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base + e0 * U * width), short(0),
+                                             ne * U * width * 4, 0x00020000);
+  };
+  // The 0e component has tensors of its own, s (forward, out) and ds (backward,
+  // in), both [E][U]: item k of the thread is channels u + 16 i of edge e, index
+  // 16 e + u = mt + 256 k.
+  constexpr int SPER = (NE * 16 + THREADS - 1) / THREADS;
+  auto has_item = [&](int k) { return NE * 16 % THREADS == 0 || mt + THREADS * k < NE * 16; };
+  auto item_off = [&](int k) { return 4 * ((mt / 16 + THREADS / 16 * k) * U + mt % 16); };
+  FloatVec<VW> v[PER][4];
+  f32x4 dsv[SPER];  // backward: ds of the next tile
+  auto load = [&](__amdgpu_buffer_rsrc_t r, int j) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[j][i] = buffer_load_f<VW>(r, off[j] + i * 64 * D1);
+  };
+  auto load_ds = [&](int64_t t) {
+    const auto r = rsrc(ds, 1, t);
+#pragma unroll
+    for (int k = 0; k < SPER; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dsv[k][i] = buffer_load_f<1>(r, item_off(k) + 64 * i)[0];
+  };
+  auto put_ds = [&] {
+#pragma unroll
+    for (int k = 0; k < SPER; ++k)
+      if (has_item(k)) reinterpret_cast<f32x4 *>(lds + 2 * M::BUF)[mt + THREADS * k] = dsv[k];
+  };
+  // s[e][u] = T[e][u][0]: irrep 0 (0e) has one component, so its column is e
+  auto store_s = [&](int64_t t, const float *b) {
+    const auto r = rsrc(s_out, 1, t);
+#pragma unroll
+    for (int k = 0; k < SPER; ++k) {
+      if (!has_item(k)) continue;
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(b + (mt / 16 + THREADS / 16 * k) * M::CS + 4 * (mt % 16));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) buffer_store_f<1>(r, item_off(k) + 64 * i, FloatVec<1>{x[i]});
     }
   };
-  auto put = [&](float *b, const float4 (&v)[PER]) {
+  auto put = [&](float *b, int j) {
+    // The task's registers as the loads left them: without this the transposing
+    // moves are made at the end of the period before, and wait for the loads there.
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      if (fi(i) >= F4) continue;
-      b[addr[i][0]] = v[i].x;
-      b[addr[i][1]] = v[i].y;
-      b[addr[i][2]] = v[i].z;
-      b[addr[i][3]] = v[i].w;
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (VW == 1) {
+        float x = v[j][i][0];
+        asm volatile("" : "+v"(x));
+        v[j][i][0] = x;
+      } else {
+        asm volatile("" : "+v"(v[j][i]));
+      }
     }
+    if (M::TASKS % THREADS != 0 && mt + THREADS * j >= M::TASKS) return;
+#pragma unroll
+    for (int q = 0; q < VW; ++q)
+      *reinterpret_cast<f32x4 *>(b + addr[j][q]) = f32x4{v[j][0][q], v[j][1][q], v[j][2][q], v[j][3][q]};
   };
   auto store = [&](int64_t t, const float *b) {
-    const int nf4 = count(t);
-    float4 *d4 = reinterpret_cast<float4 *>(dst + t * NE * U * D1);
+    const auto r = rsrc(dst, D1, t);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int f = fi(i);
-      if (f < nf4) store_stream(make_float4(b[addr[i][0]], b[addr[i][1]], b[addr[i][2]], b[addr[i][3]]), d4 + f);
+    for (int j = 0; j < PER; ++j) {
+      f32x4 x[VW];
+#pragma unroll
+      for (int q = 0; q < VW; ++q) x[q] = *reinterpret_cast<const f32x4 *>(b + addr[j][q]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        FloatVec<VW> y;
+#pragma unroll
+        for (int q = 0; q < VW; ++q) y[q] = x[q][i];
+        buffer_store_f<VW>(r, off[j] + i * 64 * D1, y);
+      }
     }
   };
-  // The tile after the next one is loaded into registers one period ahead,
-  // so its loads stay in flight across the barriers and the compute waves'
-  // write-back.
-  const int64_t G = gridDim.x;
-  int64_t t = blockIdx.x;
-  float4 v[PER];
-  if (t < n_tiles) {
-    load(t, v);
-    put(lds, v);
+  // The tile after the next one is loaded into registers one period ahead, each
+  // task's loads as soon as its registers have moved to LDS, so that a compute
+  // unit always has most of a tile's loads in flight.  Every period issues the
+  // same accesses, those of a tile that is not there with an empty descriptor:
+  // the loads and stores share one in-order counter, and behind a branch the
+  // wait for a tile's loads would also wait for the stores issued after them.
+  // tiles of period p - 1, p, p + 1 and p + 2
+  int64_t before = -1, t = blockIdx.x, next = t + gridDim.x, after = next + gridDim.x;
+  {
+    const auto r0 = rsrc(src, D1, t), r1 = rsrc(src, D1, next);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) load(r0, j);
+    if constexpr (BWD) load_ds(t);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      put(lds, j);
+      load(r1, j);
+    }
   }
-  if (t + G < n_tiles) load(t + G, v);
-  lds_sync<8>();
+  lds_sync<12>();
   int p = 0;
-  for (; t < n_tiles; t += G, ++p) {
-    // each LDS element is read (store of tile t - G) and then overwritten (tile
-    // t + G) by the same thread, so program order alone orders the two
+  for (; t < n_tiles; ++p) {
+    // each LDS element is read (store of the tile before) and then overwritten (the
+    // next tile) by the same thread, so program order alone orders the two
     float *b = lds + ((p + 1) & 1) * M::BUF;
-    if (p > 0) store(t - G, b);
-    if (t + G < n_tiles) put(b, v);
-    if (t + 2 * G < n_tiles) load(t + 2 * G, v);
-    lds_sync<8>();  // B1
-    lds_sync<8>();  // B2: the compute waves have written tile t's results
+    if constexpr (BWD) put_ds();  // read by the compute waves between B1 and B2
+    else store_s(t, lds + (p & 1) * M::BUF);  // overwritten by them after B1
+    store(before, b);
+    if constexpr (BWD) load_ds(next);
+    const auto r = rsrc(src, D1, after);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      // the loads go into the registers that put has just read: not moved above
+      // it, where they would need others
+      __builtin_amdgcn_sched_barrier(0);
+      put(b, j);
+      __builtin_amdgcn_sched_barrier(0);
+      load(r, j);
+    }
+    lds_sync<12>();  // B1
+    lds_sync<12>();  // B2: the compute waves have written this tile's results
+    before = t;
+    t = next;
+    next = after;
+    after = __builtin_amdgcn_readfirstlane(order[(p + 3) & 3]);
   }
-  if (p > 0) store(t - G, lds + ((p + 1) & 1) * M::BUF);
+  store(before, lds + ((p + 1) & 1) * M::BUF);
 }
 
 template <int LMAX, bool FULL, bool BWD>
 __global__ __launch_bounds__(kMixThreads) void mix_kernel(int64_t E, const float *__restrict__ src,
                                                           const float *__restrict__ mix,
                                                           const float *__restrict__ ds, float *__restrict__ dst,
-                                                          float *__restrict__ s_out) {
+                                                          float *__restrict__ s_out, int *__restrict__ ticket) {
   using X = XIrreps<LMAX, FULL>;
-  __shared__ float lds[2 * MixTile<X>::BUF];
-  const int64_t n_tiles = (E + kMixEdges - 1) / kMixEdges;
-  if (threadIdx.x < 256) mix_compute_role<X, BWD>(E, n_tiles, mix, ds, s_out, lds);
-  else mix_memory_role<X>(E, n_tiles, src, dst, lds);
+  using M = MixTile<X>;
+  __shared__ float4 lds4[(2 * M::BUF + (BWD ? M::NE * kU : 0)) / 4];  // tiles, ds
+  __shared__ int order[4];
+  float *lds = reinterpret_cast<float *>(lds4);
+  const int64_t n_tiles = (E + M::NE - 1) / M::NE;
+  if (threadIdx.x < 3) order[threadIdx.x] = int(blockIdx.x + threadIdx.x * gridDim.x);  // read after the first barrier
+  if (threadIdx.x < kWave * kMixComputeWaves) mix_compute_role<X, BWD>(n_tiles, mix, lds, order, ticket);
+  else mix_memory_role<X, BWD>(E, n_tiles, src, ds, dst, s_out, lds, order);
 }
 
 constexpr int kWgEdges = 4;        // edges per tile: column counts NE * (2l + 1) are multiples of 4
@@ -715,10 +956,10 @@ struct Shape {
 
 // Byte offsets of the regions of the saved and workspace buffers.
 struct SavedLayout {
-  size_t w, env, T, s, a, total;
+  size_t w, env, T, s, a, ticket, total;
 };
 struct WorkLayout {
-  size_t dT, da, dhm, ds, dw, genv, tpws, red, mixp, total, tpws_bytes;
+  size_t dT, da, dhm, ds, dw, genv, tpws, red, mixp, ticket, total, tpws_bytes;
 };
 
 SavedLayout saved_layout(const Shape &z) {
@@ -730,6 +971,7 @@ SavedLayout saved_layout(const Shape &z) {
   o.T = take(size_t(z.E) * z.U * z.d1);
   o.s = take(size_t(z.E) * z.U);
   o.a = take(size_t(z.E) * z.H);
+  o.ticket = take(1);
   o.total = at;
   return o;
 }
@@ -752,6 +994,7 @@ WorkLayout work_layout(const allegro_tp_plan *plan, const Shape &z) {
   const size_t mn = std::max({size_t(z.L + z.U) * z.H, size_t(z.H) * z.L, size_t(z.L) * z.U});
   o.red = take(size_t(red_groups(z.E)) * mn * f);
   o.mixp = take(size_t(wgrad_groups(z.E)) * z.NX * z.U * z.U * f);
+  o.ticket = take(sizeof(int));
   o.total = at;
   return o;
 }
@@ -802,20 +1045,20 @@ struct DenseOps {
   }
 
   // w = h A;  a = [h, s] B1 (after the mixing has written s);  h' = h + SiLU(a) B2
-  static void embed_weights(hipStream_t s, int64_t E, const float *h, const float *A, float *w) {
-    row<L, 0, U, 0, kProNone, kEpiStore>(s, {E, h, nullptr, A, U, 1, nullptr, w, nullptr});
+  static void embed_weights(hipStream_t s, int64_t E, const float *h, const float *A, float *w, int *ticket) {
+    row<L, 0, U, 0, kProNone, kEpiStore>(s, {E, h, nullptr, A, U, 1, nullptr, w, nullptr, ticket});
   }
   static void latent(hipStream_t s, int64_t E, const float *h, const float *sv, const float *B1, const float *B2,
                      float *a, float *h_out) {
-    row<L, U, H, 0, kProNone, kEpiStore>(s, {E, h, sv, B1, H, 1, nullptr, a, nullptr});
-    row<H, 0, L, 0, kProSilu, kEpiAdd>(s, {E, a, nullptr, B2, L, 1, h, h_out, nullptr});
+    row<L, U, H, 0, kProNone, kEpiStore>(s, {E, h, sv, B1, H, 1, nullptr, a, nullptr, nullptr});
+    row<H, 0, L, 0, kProSilu, kEpiAdd>(s, {E, a, nullptr, B2, L, 1, h, h_out, nullptr, nullptr});
   }
   // da = (dh' B2^T) * SiLU'(a);  [dhm | ds] = [dh', 0] + da B1^T;  dB2, dB1
   static void latent_vjp(hipStream_t s, int64_t E, const float *h, const float *sv, const float *a,
                          const float *B1, const float *B2, const float *dh_out, float *da, float *dhm, float *ds,
-                         float *part, float *dB1, float *dB2) {
-    row<L, 0, H, 0, kProNone, kEpiSiluGrad>(s, {E, dh_out, nullptr, B2, 1, L, a, da, nullptr});
-    row<H, 0, L + U, L, kProNone, kEpiSplitAdd>(s, {E, da, nullptr, B1, 1, H, dh_out, dhm, ds});
+                         float *part, float *dB1, float *dB2, int *ticket) {
+    row<L, 0, H, 0, kProNone, kEpiSiluGrad>(s, {E, dh_out, nullptr, B2, 1, L, a, da, nullptr, ticket});
+    row<H, 0, L + U, L, kProNone, kEpiSplitAdd>(s, {E, da, nullptr, B1, 1, H, dh_out, dhm, ds, nullptr});
     reduce<H, 0, L, kProSilu>(s, E, a, nullptr, dh_out, part, dB2);
     reduce<L, U, H, kProNone>(s, E, h, sv, da, part, dB1);
   }
@@ -823,16 +1066,17 @@ struct DenseOps {
   static void embed_vjp(hipStream_t s, int64_t E, const float *h, const float *A, const float *dw, const float *dhm,
                         float *part, float *dA, float *dh) {
     reduce<L, 0, U, kProNone>(s, E, h, nullptr, dw, part, dA);
-    row<U, 0, L, 0, kProNone, kEpiAdd>(s, {E, dw, nullptr, A, 1, U, dhm, dh, nullptr});
+    row<U, 0, L, 0, kProNone, kEpiAdd>(s, {E, dw, nullptr, A, 1, U, dhm, dh, nullptr, nullptr});
   }
 };
 
 struct DenseTable {
-  void (*embed_weights)(hipStream_t, int64_t, const float *, const float *, float *) = nullptr;
+  void (*embed_weights)(hipStream_t, int64_t, const float *, const float *, float *, int *) = nullptr;
   void (*latent)(hipStream_t, int64_t, const float *, const float *, const float *, const float *, float *,
                  float *) = nullptr;
   void (*latent_vjp)(hipStream_t, int64_t, const float *, const float *, const float *, const float *,
-                     const float *, const float *, float *, float *, float *, float *, float *, float *) = nullptr;
+                     const float *, const float *, float *, float *, float *, float *, float *, float *,
+                     int *) = nullptr;
   void (*embed_vjp)(hipStream_t, int64_t, const float *, const float *, const float *, const float *, float *,
                     float *, float *) = nullptr;
 };
@@ -859,15 +1103,16 @@ struct MixOps {
   static unsigned grid(int64_t E) {
     static const int64_t slots = resident_groups(reinterpret_cast<const void *>(&mix_kernel<LMAX, FULL, BWD>),
                                                  kMixThreads);
-    return unsigned(std::min<int64_t>(cdiv(E, kMixEdges), slots));
+    return unsigned(std::min<int64_t>(cdiv(E, MixTile<XIrreps<LMAX, FULL>>::NE), slots));
   }
-  static void forward(hipStream_t s, int64_t E, const float *T, const float *mix, float *V_out, float *sv) {
+  static void forward(hipStream_t s, int64_t E, const float *T, const float *mix, float *V_out, float *sv,
+                      int *ticket) {
     if (E == 0) return;
     hipLaunchKernelGGL((mix_kernel<LMAX, FULL, false>), dim3(grid<false>(E)), dim3(kMixThreads), 0, s, E, T, mix,
-                       nullptr, V_out, sv);
+                       nullptr, V_out, sv, ticket);
   }
   static void backward(hipStream_t s, int64_t E, const float *dV_out, const float *T, const float *mix,
-                       const float *ds, float *dT, float *part, float *dmix) {
+                       const float *ds, float *dT, float *part, float *dmix, int *ticket) {
     using X = XIrreps<LMAX, FULL>;
     // resident workgroups (one per compute unit), at most the partials the workspace holds
     static const int64_t slots = std::min<int64_t>(
@@ -875,7 +1120,7 @@ struct MixOps {
     const int64_t Gw = std::min<int64_t>(wgrad_groups(E), slots);
     if (E > 0) {
       hipLaunchKernelGGL((mix_kernel<LMAX, FULL, true>), dim3(grid<true>(E)), dim3(kMixThreads), 0, s, E, dV_out,
-                         mix, ds, dT, nullptr);
+                         mix, ds, dT, nullptr, ticket);
       hipLaunchKernelGGL((mix_wgrad_kernel<LMAX, FULL>), dim3(unsigned(Gw)), dim3(kWgThreads), 0, s, E, dV_out, T,
                          part);
     }
@@ -884,9 +1129,9 @@ struct MixOps {
 };
 
 struct MixTable {
-  void (*forward)(hipStream_t, int64_t, const float *, const float *, float *, float *) = nullptr;
+  void (*forward)(hipStream_t, int64_t, const float *, const float *, float *, float *, int *) = nullptr;
   void (*backward)(hipStream_t, int64_t, const float *, const float *, const float *, const float *, float *,
-                   float *, float *) = nullptr;
+                   float *, float *, int *) = nullptr;
 };
 
 template <int LMAX, bool FULL>
@@ -977,11 +1222,12 @@ int allegro_layer_forward(const allegro_tp_plan *plan, int L, int H, int64_t N, 
   if (!mx.forward) return fail(ALLEGRO_E_UNSUPPORTED, "no mixing kernel for this plan");
   float *w = at<float>(saved, sl.w), *env = at<float>(saved, sl.env), *T = at<float>(saved, sl.T);
   float *sv = at<float>(saved, sl.s), *a = at<float>(saved, sl.a);
-  dn.embed_weights(s, E, h, A, w);
+  int *ticket = at<int>(saved, sl.ticket);
+  dn.embed_weights(s, E, h, A, w, ticket);
   if ((rc = after("allegro_layer_forward"))) return rc;
   if ((rc = allegro_env_embed(plan, N, E, row_ptr, w, Y, env, stream))) return rc;
   if ((rc = allegro_tp_forward(plan, N, E, row_ptr, V, env, W, T, stream))) return rc;
-  mx.forward(s, E, T, Mix, V_out, sv);
+  mx.forward(s, E, T, Mix, V_out, sv, ticket);
   dn.latent(s, E, h, sv, B1, B2, a, h_out);
   return after("allegro_layer_forward");
 }
@@ -1031,8 +1277,9 @@ int allegro_layer_backward(const allegro_tp_plan *plan, int L, int H, int64_t N,
   float *dT = at<float>(workspace, wl.dT), *da = at<float>(workspace, wl.da), *dhm = at<float>(workspace, wl.dhm);
   float *ds = at<float>(workspace, wl.ds), *dw = at<float>(workspace, wl.dw), *genv = at<float>(workspace, wl.genv);
   float *red = at<float>(workspace, wl.red), *mixp = at<float>(workspace, wl.mixp);
-  dn.latent_vjp(s, E, h, sv, a, B1, B2, dh_out, da, dhm, ds, red, dB1, dB2);
-  mx.backward(s, E, dV_out, T, Mix, ds, dT, mixp, dMix);
+  int *ticket = at<int>(workspace, wl.ticket);
+  dn.latent_vjp(s, E, h, sv, a, B1, B2, dh_out, da, dhm, ds, red, dB1, dB2, ticket);
+  mx.backward(s, E, dV_out, T, Mix, ds, dT, mixp, dMix, ticket);
   if ((rc = after("allegro_layer_backward"))) return rc;
   if ((rc = allegro_tp_backward_train(plan, N, E, row_ptr, V, env, W, dT, w, Y, dV, genv, dw, dY, dW,
                                       at<void>(workspace, wl.tpws), wl.tpws_bytes, stream)))

@@ -345,3 +345,90 @@ def test_layer_replays_in_a_hip_graph(at):
         torch.cuda.synchronize()
         for a, b in zip(results, eager):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), rep
+
+
+# ------------------------------------------------------ channel mixing
+
+def _saved_product(saved, plan, N, E):
+    """T [E, 64, d1] and s [E, 64] inside a layer's saved buffer: w, env, T, s, each on a 256-byte boundary."""
+    at_, views = 0, []
+    for shape in ((E, 64), (N, 64, plan.d2), (E, 64, plan.d1), (E, 64)):
+        n = 4 * int(np.prod(shape))
+        views.append(saved[at_:at_ + n].view(torch.float32).reshape(shape))
+        at_ += (n + 255) // 256 * 256
+    return views[2], views[3]
+
+
+def _mixed(plan, mix, t, transposed):
+    """Mix_c t_c (or Mix_c^T t_c) in fp64, and the sum of the magnitudes of its terms."""
+    out, mag = torch.empty_like(t, dtype=torch.float64), torch.empty_like(t, dtype=torch.float64)
+    m = mix.double().transpose(1, 2).contiguous() if transposed else mix.double()
+    k = 0
+    for c in range(plan.n_x):
+        d = 2 * (c // 2 if plan.n_x > plan.lmax + 1 else c) + 1
+        blk = t[:, :, k:k + d].double().transpose(1, 2).reshape(-1, 64)
+        for dst, a, b in ((out, m[c], blk), (mag, m[c].abs(), blk.abs())):
+            dst[:, :, k:k + d] = (b @ a.t().contiguous()).reshape(len(t), d, 64).transpose(1, 2)
+        k += d
+    return out, mag
+
+
+# A mixed value is a sum of 64 products in fp32, split into six bf16 products each: 64 roundings of a partial
+# sum and a split error below two roundings, each at most 2^-24 of the terms' magnitudes.
+MIX_TOL = 66 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("lmax,full,tile", [(1, False, 32), (1, True, 32), (2, False, 16), (2, True, 14),
+                                            (3, False, 16), (3, True, 8)])
+def test_layer_mixing_tiles(at, lmax, full, tile):
+    """Forward and backward channel mixing around the edge tile and, with the last size, past the
+    three tiles of a workgroup that its index fixes (the rest are taken in the order of arrival)."""
+    plan, L, H = _plan(at, lmax, full), 64, 64
+    for E in (1, tile - 1, tile, tile + 1, 4 * 256 * tile + 5):
+        _note(f"[gpu] mixing lmax={lmax} full={full} E={E}")
+        deg = np.full((E + 6) // 7, 7)
+        deg[-1] -= deg.sum() - E
+        row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(lmax, full, L, H, deg, seed=E)
+        wd = {k: _t(v) for k, v in prm.items()}
+        dV = _t(dV_out)
+        args = (plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+        _, V_out, saved = at.allegro_layer_forward(*args)
+        work = torch.empty(at.allegro_layer_buffers(plan, L, H, len(deg), E)[1], dtype=torch.uint8, device=DEV)
+        at.allegro_layer_backward(*args, saved, torch.zeros_like(_t(dh_out)), dV, workspace=work)
+        T, s = _saved_product(saved, plan, len(deg), E)
+        assert torch.equal(s, T[:, :, 0])
+        ref, mag = _mixed(plan, wd["Mix"], T, False)
+        assert bool(((V_out - ref).abs() <= MIX_TOL * mag).all())
+        # with dh_out = 0 the scalars' gradient is zero, so dT (the workspace's first region) is the mixing alone
+        dT = work[:4 * E * 64 * plan.d1].view(torch.float32).reshape(E, 64, plan.d1)
+        ref, mag = _mixed(plan, wd["Mix"], dV, True)
+        assert bool(((dT - ref).abs() <= MIX_TOL * mag).all())
+
+
+@pytest.mark.parametrize("lmax,full", [(1, False), (1, True), (2, False), (2, True), (3, False), (3, True)])
+def test_layer_mixing_special_values(at, lmax, full):
+    """Infinities, NaN, values next to the largest float and subnormal ones go through the mixing as
+    through fp32 products: the backward's mixing, whose input is given."""
+    plan, L, H, E = _plan(at, lmax, full), 64, 64, 75
+    row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(lmax, full, L, H, [40, 35], seed=11)
+    big, tiny = np.float32(3.4e38), np.float32(2.0 ** -126)
+    dV_out[3, 5, 0], dV_out[20, 63, -1], dV_out[41, 0, 1], dV_out[60, 7, 2] = np.inf, -np.inf, np.nan, big
+    dV_out[10] *= tiny / 4
+    dV_out[50] *= tiny * 64
+    wd = {k: _t(v) for k, v in prm.items()}
+    wd["Mix"][:, 9, 9] = 0.0
+    dV = _t(dV_out)
+    args = (plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+    _, _, saved = at.allegro_layer_forward(*args)
+    work = torch.empty(at.allegro_layer_buffers(plan, L, H, 2, E)[1], dtype=torch.uint8, device=DEV)
+    at.allegro_layer_backward(*args, saved, torch.zeros_like(_t(dh_out)), dV, workspace=work)
+    dT = work[:4 * E * 64 * plan.d1].view(torch.float32).reshape(E, 64, plan.d1)
+    ref, mag = _mixed(plan, wd["Mix"], dV, True)
+    ref32 = ref.float()
+    assert torch.equal(torch.isnan(dT), torch.isnan(ref32))
+    assert torch.equal(torch.isinf(dT), torch.isinf(ref32)) and torch.equal(dT.isinf() * dT.sign(),
+                                                                            ref32.isinf() * ref32.sign())
+    ok = torch.isfinite(ref32)
+    assert int(ok.sum()) > ok.numel() // 2
+    # 64 partial sums may each be off by half the smallest subnormal step as well
+    assert bool(((dT - ref).abs() <= MIX_TOL * mag + 64 * 2.0 ** -150)[ok].all())
