@@ -956,7 +956,7 @@ struct Shape {
 
 // Byte offsets of the regions of the saved and workspace buffers.
 struct SavedLayout {
-  size_t w, env, T, s, a, ticket, total;
+  size_t w, env, T, s, a, total;
 };
 struct WorkLayout {
   size_t dT, da, dhm, ds, dw, genv, tpws, red, mixp, ticket, total, tpws_bytes;
@@ -971,7 +971,6 @@ SavedLayout saved_layout(const Shape &z) {
   o.T = take(size_t(z.E) * z.U * z.d1);
   o.s = take(size_t(z.E) * z.U);
   o.a = take(size_t(z.E) * z.H);
-  o.ticket = take(1);
   o.total = at;
   return o;
 }
@@ -1222,7 +1221,7 @@ int allegro_layer_forward(const allegro_tp_plan *plan, int L, int H, int64_t N, 
   if (!mx.forward) return fail(ALLEGRO_E_UNSUPPORTED, "no mixing kernel for this plan");
   float *w = at<float>(saved, sl.w), *env = at<float>(saved, sl.env), *T = at<float>(saved, sl.T);
   float *sv = at<float>(saved, sl.s), *a = at<float>(saved, sl.a);
-  int *ticket = at<int>(saved, sl.ticket);
+  int *ticket = at<int>(saved, sl.a);  // in a's region, which is written after the mixing
   dn.embed_weights(s, E, h, A, w, ticket);
   if ((rc = after("allegro_layer_forward"))) return rc;
   if ((rc = allegro_env_embed(plan, N, E, row_ptr, w, Y, env, stream))) return rc;
