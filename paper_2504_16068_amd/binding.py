@@ -13,6 +13,11 @@ from __future__ import annotations
 import ctypes
 import os
 
+# PyTorch ships its own HIP runtime with the same soname as /opt/rocm's.
+# Loading torch first makes the library bind to that one runtime; loading
+# the library first would put two HIP runtimes in the process.
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liballegro_tp.so")
 
@@ -44,11 +49,6 @@ class AllegroError(RuntimeError):
 
 
 def _load() -> ctypes.CDLL:
-    # PyTorch ships its own HIP runtime with the same soname as /opt/rocm's.
-    # Loading torch first makes the library bind to that one runtime; loading
-    # the library first would put two HIP runtimes in the process.
-    import torch  # noqa: F401
-
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run paper_2504_16068_amd.build.build() or "
                           "__graft_entry__.build() first (there is no CPU fallback)")
@@ -144,13 +144,19 @@ def allegro_tp_plan_destroy(plan: Plan):
 
 # ----------------------------------------------------------------- tensors
 
+# A call's own cost is what a small step consists of (64 atoms: five calls of
+# 11 us each, against 16 us of kernels), so the checks of an argument that is
+# right take one pass of cheap comparisons, pointers go to ctypes as plain
+# integers, and the stream handle comes without a Stream object around it.
+
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None and t.numel() > 0 else 0
 
 
 def _need(t, name, shape, dtype, device):
-    import torch
-
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape and t.device == device
+            and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device != device or t.device.type != "cuda":
@@ -163,24 +169,24 @@ def _need(t, name, shape, dtype, device):
         raise ValueError(f"{name} must be contiguous")
 
 
-def _stream(stream, device):
-    import torch
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+
+def _stream(stream, device):
+    if stream is None:
+        if _raw_stream is not None and device.index is not None:
+            return _raw_stream(device.index)
+        stream = torch.cuda.current_stream(device)
+    return stream.cuda_stream
 
 
 def _sizes(plan: Plan, row_ptr, n_edges):
-    import torch
-
     if row_ptr.dtype != torch.int64 or row_ptr.dim() != 1 or not row_ptr.is_contiguous():
         raise ValueError("row_ptr must be a contiguous 1-D int64 tensor")
     return row_ptr.numel() - 1, n_edges
 
 
 def allegro_env_embed(plan: Plan, row_ptr, w, Y, env=None, stream=None):
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, w.shape[0])
     _need(w, "w", (e, plan.U), torch.float32, dev)
@@ -194,8 +200,6 @@ def allegro_env_embed(plan: Plan, row_ptr, w, Y, env=None, stream=None):
 
 
 def allegro_tp_forward(plan: Plan, row_ptr, x, env, path_w, out=None, stream=None):
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, x.shape[0])
     _need(x, "x", (e, plan.U, plan.d1), torch.float32, dev)
@@ -211,8 +215,6 @@ def allegro_tp_forward(plan: Plan, row_ptr, x, env, path_w, out=None, stream=Non
 
 def allegro_tp_backward(plan: Plan, row_ptr, x, env, path_w, grad_out, w, Y, outs=None, stream=None):
     """Returns (grad_x, grad_env, grad_w, grad_Y)."""
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, x.shape[0])
     _need(x, "x", (e, plan.U, plan.d1), torch.float32, dev)
@@ -244,8 +246,6 @@ def allegro_tp_backward_workspace(plan: Plan, n_centers: int) -> int:
 def allegro_tp_backward_train(plan: Plan, row_ptr, x, env, path_w, grad_out, w, Y, outs=None, workspace=None,
                               stream=None):
     """Returns (grad_x, grad_env, grad_w, grad_Y, grad_path_w); workspace is a uint8 device tensor or None."""
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, x.shape[0])
     _need(x, "x", (e, plan.U, plan.d1), torch.float32, dev)
@@ -278,8 +278,6 @@ def allegro_tp_backward_train(plan: Plan, row_ptr, x, env, path_w, grad_out, w, 
 def allegro_tp_backward_train_noalloc(plan: Plan, row_ptr, x, env, path_w, grad_out, w, Y, outs=None, stream=None):
     """Returns (grad_x, grad_env, grad_w, grad_Y, grad_path_w); the library keeps the
     partial sums in its own static device memory (no workspace)."""
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, x.shape[0])
     _need(x, "x", (e, plan.U, plan.d1), torch.float32, dev)
@@ -305,8 +303,6 @@ def allegro_tp_backward_train_noalloc(plan: Plan, row_ptr, x, env, path_w, grad_
 
 def allegro_sh_forward(plan: Plan, vec, Y=None, stream=None):
     """Y [E, d2] float32 from edge vectors vec [E, 3] float64."""
-    import torch
-
     dev = vec.device
     e = vec.shape[0]
     _need(vec, "vec", (e, 3), torch.float64, dev)
@@ -319,8 +315,6 @@ def allegro_sh_forward(plan: Plan, vec, Y=None, stream=None):
 
 def allegro_sh_backward(plan: Plan, vec, grad_Y, grad_vec=None, stream=None):
     """grad_vec [E, 3] float64 from vec [E, 3] float64 and grad_Y [E, d2] float32."""
-    import torch
-
     dev = vec.device
     e = vec.shape[0]
     _need(vec, "vec", (e, 3), torch.float64, dev)
@@ -349,8 +343,6 @@ def allegro_layer_buffers(plan: Plan, L: int, H: int, n_centers: int, n_edges: i
 
 
 def _bytes_buffer(t, need, name, device):
-    import torch
-
     if t is None:
         return torch.empty(max(need, 16), dtype=torch.uint8, device=device)
     if t.device != torch.device(device) or not t.is_contiguous():
@@ -363,8 +355,6 @@ def _nbytes(t):
 
 
 def _layer_inputs(plan, L, H, row_ptr, h, V, Y, weights):
-    import torch
-
     dev = row_ptr.device
     n, e = _sizes(plan, row_ptr, V.shape[0])
     _need(h, "h", (e, L), torch.float32, dev)
@@ -378,8 +368,6 @@ def _layer_inputs(plan, L, H, row_ptr, h, V, Y, weights):
 def allegro_layer_forward(plan: Plan, L: int, H: int, row_ptr, h, V, Y, weights, h_out=None, V_out=None,
                           saved=None, stream=None):
     """Returns (h_out, V_out, saved); weights maps A, W, Mix, B1, B2 to device tensors."""
-    import torch
-
     dev, n, e = _layer_inputs(plan, L, H, row_ptr, h, V, Y, weights)
     sv_need, _ = allegro_layer_buffers(plan, L, H, n, e)
     h_out = torch.empty_like(h) if h_out is None else h_out
@@ -396,8 +384,6 @@ def allegro_layer_forward(plan: Plan, L: int, H: int, row_ptr, h, V, Y, weights,
 def allegro_layer_backward(plan: Plan, L: int, H: int, row_ptr, h, V, Y, weights, saved, dh_out, dV_out,
                            outs=None, workspace=None, stream=None):
     """Returns a dict of gradients: h, V, Y and the weights A, W, Mix, B1, B2."""
-    import torch
-
     dev, n, e = _layer_inputs(plan, L, H, row_ptr, h, V, Y, weights)
     _need(dh_out, "dh_out", (e, L), torch.float32, dev)
     _need(dV_out, "dV_out", (e, plan.U, plan.d1), torch.float32, dev)
