@@ -9,7 +9,9 @@
 //     split between the two channel halves.
 //   * The center's slabs (64 consecutive [U][d1] rows, contiguous in HBM) are
 //     dealt to its waves; each slab moves through an LDS tile with 16-byte
-//     coalesced accesses and each lane then works on its own row.
+//     coalesced accesses and each lane then works on its own row.  (The forward
+//     at lmax <= 2, which has no sums over edges, deals the slabs of the whole
+//     edge list instead and looks up each edge's center.)
 //   * Direct kernels (forward at lmax <= 2, inference backward at every
 //     lmax, training backward at lmax <= 2): path weights W[:, u] and
 //     env[n, u, :] are loaded once per center into VGPRs and the contraction
@@ -344,59 +346,141 @@ struct KernelTraits {
 // one workgroup (with two channel halves, U = 128, the first NW/2 waves take
 // half 0 and the rest half 1); each wave streams its slabs through its own
 // LDS tile.  With many waves on one center the concurrently streamed HBM
-// regions are few and contiguous: a standalone probe of the forward's access
-// pattern measured 4.98 TB/s with one wave per center and 5.51 TB/s with 16.
+// regions are few and contiguous: a standalone probe of a per-center copy
+// measured 4.98 TB/s with one wave per center and 5.51 TB/s with 16.
 // That pays where the kernel is HBM-bound (lmax <= 2).  The training backward,
 // which also holds the path-weight sums, is bound by VALU issue; with fewer
 // waves per center more workgroups fit on a compute unit and overlap one
 // center's reduction phases with another's streaming.  The counts are the
-// fastest of 1, 2, 4, 8 and 16 measured for each kernel on the MI355X.  (At
-// lmax 3 the forward is tp_matrix_kernel and the backward tp_mfma_bwd_kernel.)
+// fastest of 1, 2, 4, 8 and 16 measured for each kernel on the MI355X.  (The
+// training backward at lmax 3 is tp_mfma_bwd_kernel.)
 template <class Core, int U>
 struct TPWaves {
   static constexpr bool kHigh = Core::LMAX >= 3, kWide = U > 64;
-  static constexpr int kFwd = 16;  // lmax <= 2
   static constexpr int bwd(bool wg) { return wg ? 4 : (kHigh ? (kWide ? 8 : 4) : 16); }
 };
 
 // ------------------------------------------------------ tensor product fwd
-template <class Core, int U, int NW = TPWaves<Core, U>::kFwd>
-__global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::kFwdOccupancy))) void tp_forward_kernel(const int64_t *__restrict__ row_ptr,
-                                                           const float *__restrict__ x,
-                                                           const float *__restrict__ env,
-                                                           const float *__restrict__ path_w,
-                                                           float *__restrict__ out) {
+// The center of edge e: the n in [lo, hi) with row_ptr[n] <= e < row_ptr[n + 1],
+// searched by the whole wave, which narrows the range 64-fold per step (one
+// load per lane).  A first window of 64 centers around `guess` usually holds
+// it.  Every index stays in [lo, hi] and the range shrinks every step, also
+// for a row_ptr that is not sorted.
+__device__ __forceinline__ int64_t find_center(const int64_t *__restrict__ row_ptr, int64_t lo, int64_t hi, int64_t e,
+                                               int64_t guess, int lane) {
+  int64_t w0 = guess < lo ? lo : guess, w1 = guess + kWave - 1;
+  if (w1 > hi) w1 = hi;
+  if (w0 < w1) {
+    const int64_t i = w0 + lane;
+    const uint64_t m = __ballot(i <= w1 && row_ptr[i <= w1 ? i : w1] <= e);
+    const int cnt = __builtin_popcountll(m);
+    if (cnt > 0 && cnt <= int(w1 - w0)) return w0 + cnt - 1;
+  }
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave;
+    const int64_t i = lo + (lane + 1) * step;
+    const uint64_t m = __ballot(i < hi && row_ptr[i < hi ? i : hi] <= e);
+    lo += __builtin_popcountll(m) * step;
+    if (lo >= hi) lo = hi - 1;
+    if (lo + step < hi) hi = lo + step;
+  }
+  return lo;
+}
+
+// One slab's float4 in registers, loaded with a buffer descriptor whose range
+// ends with the tensor: what lies past it reads zeros.
+template <int U, int D>
+struct SlabRegs {
+  static constexpr int SF4 = TileShape<D>::SF4, PER = (SF4 + kWave - 1) / kWave;
+  f32x4 v[PER];
+  __device__ __forceinline__ void load(const float *__restrict__ src, int64_t eb, int64_t E, int t, int lane) {
+    const int64_t left = E - eb;  // edges from the slab's first on
+    constexpr int G = Lanes<U>::G;
+    const int64_t base = left > 0 ? (eb * U + t * kWave) * D : 0;
+    const int bytes = left <= 0 ? 0 : U >= kWave ? kWave * D * 4 : int(left < G ? left : G) * U * D * 4;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(src + base), short(0), bytes, 0x00020000);
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      v[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, 16 * (lane + kWave * k), 0, 2));
+  }
+  __device__ __forceinline__ void put(float4 *tile, int lane) const {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int f = lane + kWave * k;
+      if (SF4 % kWave == 0 || f < SF4) tile[TileShape<D>::pos(f)] = make_float4(v[k].x, v[k].y, v[k].z, v[k].w);
+    }
+  }
+};
+
+// out = TP(x, env) over the flat list of edges (lmax <= 2): a wave takes S
+// consecutive slabs (with two channel halves, of its half), a workgroup four
+// waves' worth, and workgroups start in edge order.  The center of an edge is
+// found by search while its x slab is on the way.  Bound by HBM (and the path
+// weights that each wave reads from L1: two slabs a wave; with three or four
+// the tiles, env rows and weights no longer fit 128 registers).  A workgroup
+// of 16 waves per center took 1.76 ms on the headline's 9.7 GB (20,000
+// centers, U = 64), this 1.69; at 6.7 edges per center, where most of those
+// waves had nothing to do, 233 -> 160 us for 100,000 edges; 1,000 centers at
+// U = 32, 48 -> 44 us.
+// Few slabs (under 16 per compute unit with two a wave) go one to a wave:
+// 1,139 edges at U = 16, 4.0 -> 3.3 us.
+constexpr int kFwdWaves = 4;
+constexpr int64_t kFwdPairSlabs = 256 * 16 * 2;  // slabs from which a wave takes two
+
+template <class Core, int U, int S>
+__global__ __launch_bounds__(kWave * kFwdWaves) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::kFwdOccupancy)))
+void tp_forward_kernel(int64_t N, int64_t E, const int64_t *__restrict__ row_ptr, const float *__restrict__ x,
+                       const float *__restrict__ env, const float *__restrict__ path_w, float *__restrict__ out) {
   using L = Lanes<U>;
-  constexpr int D1 = Core::D1, D2 = Core::D2, WPT = NW / L::CPL;
+  constexpr int D1 = Core::D1, D2 = Core::D2;
   constexpr int TF4 = TileShape<D1>::SF4;  // one slab per tile
-  static_assert(NW % L::CPL == 0, "waves split evenly over the channel halves");
-  __shared__ float4 tiles[NW * TileShape<D1>::LF4];
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, ul = lane % L::LPE;
-  const int t = wave / WPT, first = wave % WPT;
+  __shared__ float4 tiles[kFwdWaves * TileShape<D1>::LF4];
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave), lane = threadIdx.x % kWave;
+  const int64_t gw = int64_t(blockIdx.x) * kFwdWaves + wave;  // of this launch's waves
+  const int t = int(gw % L::CPL), u = lane % L::LPE + t * kWave;
+  const int64_t first = gw / L::CPL * (S * L::G);  // the wave's first edge
   float4 *tile = tiles + wave * TileShape<D1>::LF4;
   float *tile_f = reinterpret_cast<float *>(tile);
-  const int64_t n = blockIdx.x;
-  const int64_t e0 = row_ptr[n], e1 = row_ptr[n + 1];
-  const int64_t n_slabs = Slabs<U>::count(e1 - e0);
-  const int u = ul + t * kWave;
+  // every slab's loads first: the search, the weights and env arrive under them
+  SlabRegs<U, D1> xs[S];
+#pragma unroll
+  for (int k = 0; k < S; ++k) xs[k].load(x, first + k * L::G, E, t, lane);
   RegWeights<Core::NP> wr;
   wr.load(path_w, U, u);
-  float er[D2];
-  load_row<D2>(env + (n * U + u) * D2, er);
-  for (int64_t s = first; s < n_slabs; s += WPT) {
-    tile_load<U, D1, TF4>(x, tile, e0, e1, s, 1, t, lane);
+  int64_t c = int64_t(double(first) / double(E) * double(N)) - kWave / 2, c_end = -1;  // guess; last edge + 1 of c
+  int64_t lane_c[S];
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    lane_c[k] = 0;
+#pragma unroll
+    for (int g = 0; g < L::G; ++g) {  // the slab's edges, in order
+      const int64_t eg = first + k * L::G + g, e = eg < E ? eg : E - 1;
+      if (e >= c_end) {
+        c = find_center(row_ptr, 0, N, e, c, lane);
+        c_end = row_ptr[c + 1];
+      }
+      if (L::G == 1 || lane / L::LPE == g) lane_c[k] = c;
+    }
+  }
+  float er[S][D2];
+#pragma unroll
+  for (int k = 0; k < S; ++k) load_row<D2>(env + (lane_c[k] * U + u) * D2, er[k]);
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    const int64_t eb = first + k * L::G;  // the slab's first edge
+    xs[k].put(tile, lane);
     lds_sync<1>();
-    if (row_valid<U>(e0, e1, s, lane)) {
+    if (row_valid<U>(eb, E, 0, lane)) {
       float *row = tile_f + lane * TileShape<D1>::RS;
       float xr[D1], orow[D1];
 #pragma unroll
       for (int i = 0; i < D1; ++i) xr[i] = row[i];
-      Core::fwd(xr, er, wr, orow);
+      Core::fwd(xr, er[k], wr, orow);
 #pragma unroll
       for (int i = 0; i < D1; ++i) row[i] = orow[i];
     }
     lds_sync<1>();
-    tile_store<U, D1, TF4>(out, tile, e0, e1, s, 1, t, lane);
+    if (eb < E) tile_store<U, D1, TF4>(out, tile, eb, E, 0, 1, t, lane);
     lds_sync<1>();
   }
 }
@@ -1749,8 +1833,9 @@ int noalloc_scratch(float **out) {
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 using EnvFn = void (*)(dim3, hipStream_t, int64_t, const int64_t *, const float *, const float *, float *);
-using FwdFn = void (*)(dim3, hipStream_t, const int64_t *, const float *, const float *, const float *, float *);
-using BwdFn = void (*)(dim3, hipStream_t, const int64_t *, const float *, const float *, const float *, const float *,
+using FwdFn = void (*)(int64_t, int64_t, hipStream_t, const int64_t *, const float *, const float *, const float *,
+                       float *);
+using BwdFn = void (*)(dim3, int64_t, hipStream_t, const int64_t *, const float *, const float *, const float *, const float *,
                        const float *, const float *, float *, float *, float *, float *, float *, WaitCfg);
 
 template <int U, int D2, bool DET>
@@ -1759,14 +1844,22 @@ void launch_env(dim3 grid, hipStream_t s, int64_t N, const int64_t *rp, const fl
 }
 
 template <class Core, int U>
-void launch_fwd(dim3 grid, hipStream_t s, const int64_t *rp, const float *x, const float *env, const float *pw,
-                float *out) {
-  if constexpr (Core::LMAX >= 3)
-    hipLaunchKernelGGL((tp_matrix_kernel<Core, U, TPMFwd<Core::LMAX, Core::FULL>>), grid, dim3(kMFwdThreads<Core>), 0,
-                       s, rp, x, env, pw, out);
-  else
-    hipLaunchKernelGGL((tp_forward_kernel<Core, U>), grid, dim3(kWave * TPWaves<Core, U>::kFwd), 0, s, rp, x, env, pw,
-                       out);
+void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env,
+                const float *pw, float *out) {
+  if constexpr (Core::LMAX >= 3) {
+    hipLaunchKernelGGL((tp_matrix_kernel<Core, U, TPMFwd<Core::LMAX, Core::FULL>>), dim3(unsigned(N)),
+                       dim3(kMFwdThreads<Core>), 0, s, rp, x, env, pw, out);
+  } else {
+    using L = Lanes<U>;
+    auto launch = [&](auto slabs) {
+      constexpr int S = decltype(slabs)::value;
+      const int64_t waves = (E + S * L::G - 1) / (S * L::G) * L::CPL;
+      hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((waves + kFwdWaves - 1) / kFwdWaves)),
+                         dim3(kWave * kFwdWaves), 0, s, N, E, rp, x, env, pw, out);
+    };
+    if (E * L::CPL / L::G < kFwdPairSlabs) launch(std::integral_constant<int, 1>{});
+    else launch(std::integral_constant<int, 2>{});
+  }
 }
 
 // Persistent grid of the matrix-core backward: the workgroups resident on the
@@ -1811,8 +1904,10 @@ int64_t mfma_pw_rounds(int64_t N) {
   return int64_t(mfma_grid<FULL, U, true>(N)) * MfmaShape<FULL>::NW / (U / MfmaShape<FULL>::CPW);
 }
 
+constexpr int64_t kFewCenters = 512;  // centers below which one workgroup per compute unit is all there is
+
 template <class Core, int U, bool WG>
-void launch_bwd(dim3 grid, hipStream_t s, const int64_t *rp, const float *x, const float *env, const float *pw,
+void launch_bwd(dim3 grid, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env, const float *pw,
                 const float *g, const float *w, const float *Y, float *gx, float *genv, float *gw, float *gy,
                 float *pw_part, WaitCfg wcfg) {
   if constexpr (Core::LMAX >= 3 && WG) {
@@ -1825,8 +1920,27 @@ void launch_bwd(dim3 grid, hipStream_t s, const int64_t *rp, const float *x, con
                        dim3(MfmaShape<Core::FULL>::THREADS), 0, s, N, rp, x, env, pw, g, gx, genv, pw_part, wcfg);
     hipLaunchKernelGGL((embedding_vjp_kernel<U, Core::D2, 4>), grid, dim3(kWave * 4), 0, s, rp, genv, w, Y, gw, gy);
   } else {
-    hipLaunchKernelGGL((tp_backward_kernel<Core, U, WG>), grid, dim3(kWave * TPWaves<Core, U>::bwd(WG)), 0, s, rp, x,
-                       env, pw, g, w, Y, gx, genv, gw, gy, pw_part);
+    auto launch = [&](auto waves) {
+      constexpr int NW = decltype(waves)::value;
+      hipLaunchKernelGGL((tp_backward_kernel<Core, U, WG, NW>), grid, dim3(kWave * NW), 0, s, rp, x, env, pw, g, w, Y,
+                         gx, genv, gw, gy, pw_part);
+    };
+    constexpr int NW = TPWaves<Core, U>::bwd(WG);
+    if constexpr (NW == 16) {
+      // Waves a center's slabs cannot keep busy only hold their compute unit
+      // (one workgroup of 16 fits): with several centers per unit, fewer waves
+      // for fewer slabs per center.  Inference backward, 16 / 8 / 4 waves, us:
+      // 52 slabs (U = 64) 2720 / 2860 / 2910, 26 (U = 64) 486 / 422 / 434, 13
+      // (U = 64) 445 / 367 / 321, 13 (U = 16) 144 / 113 / 116, 6.7 (U = 64)
+      // 481 / 374 / 294, 5.4 (U = 16) 173 / 97 / 78; 26 (U = 32) 79 / 78 / 82, where the
+      // longer sums per wave are not worth it.
+      const int64_t N = grid.x, slabs = E * U / kWave;
+      if (N >= kFewCenters && slabs < 16 * N) launch(std::integral_constant<int, 4>{});
+      else if (N >= kFewCenters && slabs < 24 * N) launch(std::integral_constant<int, 8>{});
+      else launch(std::integral_constant<int, 16>{});
+    } else {
+      launch(std::integral_constant<int, NW>{});
+    }
   }
 }
 
@@ -2063,7 +2177,7 @@ int allegro_tp_forward(const allegro_tp_plan *plan, int64_t N, int64_t E, const 
   if ((plan->flags & ALLEGRO_VALIDATE) && (rc = validate_csr(mp, N, E, row_ptr, s))) return rc;
   const Kernels k = select(plan);
   if (!k.fwd) return fail(ALLEGRO_E_UNSUPPORTED, "no kernel for this plan");
-  k.fwd(dim3(unsigned(N)), s, row_ptr, x, env, path_w, out);
+  k.fwd(N, E, s, row_ptr, x, env, path_w, out);
   return after_launch("allegro_tp_forward");
 }
 
@@ -2085,7 +2199,7 @@ int allegro_tp_backward(const allegro_tp_plan *plan, int64_t N, int64_t E, const
   if ((plan->flags & ALLEGRO_VALIDATE) && (rc = validate_csr(mp, N, E, row_ptr, s))) return rc;
   const Kernels k = select(plan);
   if (!k.bwd) return fail(ALLEGRO_E_UNSUPPORTED, "no kernel for this plan");
-  k.bwd(dim3(unsigned(N)), s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, nullptr,
+  k.bwd(dim3(unsigned(N)), E, s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, nullptr,
         WaitCfg{plan->spin_limit, nullptr});
   return after_launch("allegro_tp_backward");
 }
@@ -2143,7 +2257,7 @@ int allegro_tp_backward_train(const allegro_tp_plan *plan, int64_t N, int64_t E,
   const Kernels k = select(plan);
   if (!k.bwd_wg) return fail(ALLEGRO_E_UNSUPPORTED, "no kernel for this plan");
   float *part = static_cast<float *>(workspace);
-  k.bwd_wg(dim3(unsigned(N)), s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, part,
+  k.bwd_wg(dim3(unsigned(N)), E, s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, part,
            WaitCfg{plan->spin_limit, validate ? plan->status : nullptr});
   if ((rc = after_launch("allegro_tp_backward_train"))) return rc;
   const unsigned cb = unsigned((cols + 255) / 256);
@@ -2202,7 +2316,7 @@ int allegro_tp_backward_train_noalloc(const allegro_tp_plan *plan, int64_t N, in
     // the matrix-core kernel's per-wave rows fit the scratch at any N
     static_assert(kNoAllocFloats >= int64_t(kMaxPwRounds) * 128 * 68, "per-wave rows fit the scratch");
     const int64_t rounds = k.pw_rounds(N);  // at most kMaxPwRounds
-    k.bwd_wg(dim3(unsigned(N)), s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, scr,
+    k.bwd_wg(dim3(unsigned(N)), E, s, row_ptr, x, env, path_w, grad_out, w, Y, grad_x, grad_env, grad_w, grad_Y, scr,
              wcfg);
     pw_sum_rows(s, rounds, cols, int(plan->table.paths.size()), scr, grad_path_w);
     if ((rc = after_launch("allegro_tp_backward_train_noalloc"))) return rc;
@@ -2216,7 +2330,7 @@ int allegro_tp_backward_train_noalloc(const allegro_tp_plan *plan, int64_t N, in
     const int64_t n0 = c * lay.centers, n1 = std::min(N, n0 + lay.centers);
     // the chunk's centers as a CSR of their own: row_ptr values stay absolute
     // edge indices, center-indexed tensors are offset to the chunk's first center
-    k.bwd_wg(dim3(unsigned(n1 - n0)), s, row_ptr + n0, x, env + n0 * ud2, path_w, grad_out, w, Y, grad_x,
+    k.bwd_wg(dim3(unsigned(n1 - n0)), E, s, row_ptr + n0, x, env + n0 * ud2, path_w, grad_out, w, Y, grad_x,
              grad_env + n0 * ud2, grad_w, grad_Y, part, wcfg);
     hipLaunchKernelGGL(pw_reduce_rows_kernel, dim3(cb, kPwChunks), dim3(256), 0, s, n1 - n0, cols, part, ranges);
     pw_sum_rows(s, kPwChunks, cols, 0, ranges, chunk_rows + c * cols);

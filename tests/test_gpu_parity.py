@@ -677,3 +677,41 @@ def test_step_replays_in_a_hip_graph(at):
         torch.cuda.synchronize()
         for a, b in zip(results, eager):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), rep
+
+
+# ------------------------------------------- launch rules of the direct kernels
+
+@pytest.mark.parametrize("lmax,U,n,n_edges", [
+    # 512 centers: 4 waves a center below 16 slabs per center on average, 8 below 24, then 16; the
+    # forward takes two slabs a wave from 8192 slabs on
+    (1, 64, 512, 8191), (1, 64, 512, 8192), (1, 64, 512, 12287), (1, 64, 512, 12288), (1, 64, 511, 8193),
+    (2, 16, 600, 4097), (2, 32, 600, 1203), (2, 128, 520, 4097),
+])
+def test_launch_rules_parity(at, lmax, U, n, n_edges):
+    _note(f"[gpu] launch rules lmax={lmax} U={U} N={n} E={n_edges}")
+    rng = np.random.default_rng(n_edges)
+    degrees = np.bincount(rng.integers(0, n, n_edges), minlength=n)
+    data = _synthetic(lmax, lmax == 2, U, degrees, seed=n_edges)
+    gpu = _np(_run_gpu(at, _plan(at, lmax, U, lmax == 2), *data))
+    t, *ref = _oracle(lmax, lmax == 2, *data)
+    _compare(t, gpu, ref, f"lmax{lmax} U{U} N{n} E{n_edges}")
+
+
+@pytest.mark.parametrize("U", [16, 32, 64, 128])
+def test_forward_finds_centers_among_empty_ones(at, U):
+    """The forward at lmax <= 2 looks up each edge's center: long runs of empty centers before,
+    between and after the others, several centers within one slab, and N = 1."""
+    for n, at_ in ((70001, [0, 1, 2, 63, 64, 127, 30000, 30001, 69999, 70000]), (70001, [70000]), (70001, [0]), (1, [0]),
+                   (65, [64]), (4097, [1, 4095])):
+        degrees = np.zeros(n, dtype=np.int64)
+        degrees[at_] = 1 + np.arange(len(at_)) % 4
+        _note(f"[gpu] sparse centers U={U} N={n} E={degrees.sum()}")
+        row_ptr, x, w, y, pw, g = _synthetic(2, True, U, degrees, seed=n + U)
+        plan = _plan(at, 2, U, True)
+        env, out, _ = _np(_run_gpu(at, plan, row_ptr, x, w, y, pw, g))
+        dense = np.concatenate([[0], np.cumsum(degrees[at_])]).astype(np.int64)
+        t = otp.TensorProduct(2, True)
+        renv = otp.env_embed(dense, w, y)
+        assert block_rel_err(env[at_], renv, t.env_slices) <= FWD_TOL and np.count_nonzero(env) == np.count_nonzero(
+            env[at_])
+        assert block_rel_err(out, t.forward(dense, x, renv, pw), t.x_slices) <= FWD_TOL
