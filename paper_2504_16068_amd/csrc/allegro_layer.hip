@@ -10,10 +10,11 @@
 // conflicts; A and B always use the same order, so every product pairs the
 // same k.
 //
-//   row_gemm_kernel     C[E][N] = X[E][K] B[K][N], X = [x1 | x2] staged in LDS,
-//                       with a fused prologue (SiLU) and epilogue (add,
-//                       SiLU-gradient scale, column split): w = h A,
-//                       a = [h, s] B1, h' = h + SiLU(a) B2 and their VJPs
+//   row_gemm_kernel     C[E][N] = X[E][K] B[K][N], X staged in LDS, with an
+//                       optional addend: w = h A and dh = dhm + dw A^T
+//   latent_chain_kernel the latent update a = [h, s] B1, h' = h + SiLU(a) B2 or
+//                       its VJP in one pass, both products in fp32 through
+//                       split operands on the bf16 matrix cores
 //   reduce_gemm_kernel  G[M][N] = sum_e P[e][M] Q[e][N] (dA, dB1, dB2):
 //                       persistent workgroups with register accumulators,
 //                       one partial per workgroup, then colsum_kernel
@@ -75,51 +76,84 @@ struct XIrreps {
   static constexpr int off(int c) { return c == 0 ? 0 : off(c - 1) + dim(c - 1); }
 };
 
+// ------------------------------------------------------ split products
+// fp32 products on the bf16 matrix cores.  x = h + m + l with h = bf16(x),
+// m = bf16(x - h), l = x - h - m: 8 significant bits each, rounded to nearest,
+// so the three hold all 24 bits of x exactly (both subtractions are exact).
+// Of the nine products of two split operands the six of weight 2^-16 and more
+// are summed (in fp32, by the matrix core), the small ones first; the three
+// dropped are below 2^-26 of the product, a quarter of the rounding of one
+// fp32 product.  The matrix core takes bf16 subnormals as zero, so both
+// operands are scaled by kSplitScale first: the smallest part of any fp32
+// value, 2^-149, is then a normal number.  The sum comes back through
+// kSplitUnscale; what overflows for the scale (or is infinite to begin with)
+// leaves a sum that is not finite, and the caller redoes it in fp32.
+//
+// The matrix core rounds its bf16 sums down, not to nearest: the values carry a
+// mean error of about -1e-8 of their size.  Where a sum over every edge follows
+// directly (latent_chain_kernel, then dB1 and dB2) that shows: dB1's error rose
+// from 5.1e-7 to 5.6e-7.  There half of a sum's steps are taken with negated
+// weights into an accumulator of their own and subtracted at the end, where the
+// two means cancel.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
+struct Split8 {
+  bf16x8 h, m, l;
+};
+
+// The packed bf16 parts of two values.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
+  const f32x2 r = {x0 - __builtin_bit_cast(float, h << 16), x1 - __builtin_bit_cast(float, h & 0xffff0000u)};
+  m = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+  const f32x2 q = {r.x - __builtin_bit_cast(float, m << 16), r.y - __builtin_bit_cast(float, m & 0xffff0000u)};
+  l = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, bf16x2));
+}
+
+__device__ __forceinline__ Split8 split8(const float (&x)[8], float scale = kSplitScale) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 h, m, l;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t hb, mb, lb;
+    split2(scale * x[2 * i], scale * x[2 * i + 1], hb, mb, lb);
+    h[i] = hb;
+    m[i] = mb;
+    l[i] = lb;
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+__device__ __forceinline__ f32x4 mfma_split(const Split8 &a, const Split8 &b, f32x4 c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b.h, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.l, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.m, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.h, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.m, c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, c, 0, 0, 0);
+}
+
 // ------------------------------------------------------------- row GEMM
-enum { kProNone = 0, kProSilu = 1 };
-enum { kEpiStore = 0, kEpiAdd = 1, kEpiSiluGrad = 2, kEpiSplitAdd = 3 };
+enum { kProNone = 0, kProSilu = 1 };   // elementwise step on the rows of reduce_gemm_kernel's P
+enum { kEpiStore = 0, kEpiAdd = 1 };   // row_gemm_kernel's result, or with d added
 
 struct RowGemmArgs {
   int64_t E;
-  const float *x1, *x2;  // X = [x1 | x2], [E][K1] and [E][K2]
-  const float *b;        // B[k][n] = b[k * b_rs + n * b_cs]
+  const float *x;  // [E][K]
+  const float *b;  // B[k][n] = b[k * b_rs + n * b_cs]
   int b_rs, b_cs;
-  const float *d;        // addend (kEpiAdd, kEpiSplitAdd) or pre-activation (kEpiSiluGrad)
-  float *c, *c2;         // output; kEpiSplitAdd: columns < N1 to c, the rest to c2
-  int *ticket;           // set to zero for the mixing kernel launched after this one (may be null)
+  const float *d;  // addend (kEpiAdd)
+  float *c;
+  int *ticket;     // set to zero for the mixing kernel launched after this one (may be null)
 };
 
 constexpr int kRowTile = 64;  // rows per workgroup tile
 
 // Stages rows r0 .. r0 + 63 of x [E][KX] into columns col0 .. col0 + KX - 1 of
-// the LDS tile (row stride XS), zero past the last row, with an optional
-// elementwise prologue.  All of a thread's loads are issued before any of its
-// LDS writes, so their latencies overlap.
-template <int KX, int PRO>
-__device__ __forceinline__ void stage_rows(const float *__restrict__ x, int64_t r0, int rows, float *xs, int XS,
-                                           int col0, int tid) {
-  constexpr int F4 = kRowTile * KX / 4, PER = (F4 + kThreads - 1) / kThreads;
-  float4 v[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int f = tid + kThreads * i, r = f / (KX / 4), k = 4 * (f % (KX / 4));
-    v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (f < F4 && r < rows) v[i] = *reinterpret_cast<const float4 *>(x + (r0 + r) * KX + k);
-  }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int f = tid + kThreads * i, r = f / (KX / 4), k = 4 * (f % (KX / 4));
-    if (f >= F4) continue;
-    float4 u = v[i];
-    if constexpr (PRO == kProSilu) {
-      u.x = silu(u.x); u.y = silu(u.y); u.z = silu(u.z); u.w = silu(u.w);
-    }
-    *reinterpret_cast<float4 *>(xs + r * XS + col0 + k) = u;
-  }
-}
-
-// stage_rows in two halves, so that a tile's loads can be in flight while the
-// previous tile is multiplied: the loads into registers, then the LDS writes.
+// an LDS tile (row stride XS), zero past the last row, with an optional
+// elementwise prologue, in two halves, so that a tile's loads can be in flight
+// while the previous tile is multiplied: the loads into registers, then the LDS
+// writes.
 template <int KX>
 struct RowRegs {
   static constexpr int F4 = kRowTile * KX / 4, PER = (F4 + kThreads - 1) / kThreads;
@@ -154,14 +188,14 @@ struct RowRegs {
 // and writes its output as whole rows, 16 bytes per lane and consecutive
 // lanes along a row: written straight from the accumulators, each store
 // instruction would cover 64-byte pieces of four rows.
-template <int K1, int K2, int N, int N1, int PRO, int EPI>
+template <int K, int N, int EPI>
 __global__ __launch_bounds__(kThreads) void row_gemm_kernel(RowGemmArgs g) {
-  constexpr int K = K1 + K2, XS = K + 4;  // row stride: the 16 rows of an A read hit distinct banks
-  constexpr int OS = N + 4;               // row stride of the product tile
-  constexpr int NJ = N / 64;              // column tiles per wave
+  constexpr int XS = K + 4;   // row stride: the 16 rows of an A read hit distinct banks
+  constexpr int OS = N + 4;   // row stride of the product tile
+  constexpr int NJ = N / 64;  // column tiles per wave
   constexpr int LDSF = kRowTile * (XS > OS ? XS : OS);
   constexpr int OF4 = kRowTile * N / 4, OPER = OF4 / kThreads;  // product float4 per thread
-  static_assert(K1 % 16 == 0 && K2 % 16 == 0 && N % 64 == 0 && N1 % 16 == 0 && OF4 % kThreads == 0, "tile shape");
+  static_assert(K % 16 == 0 && N % 64 == 0 && OF4 % kThreads == 0, "tile shape");
   __shared__ float4 xs4[LDSF / 4];
   float *xs = reinterpret_cast<float *>(xs4);
   const int tid = threadIdx.x, wave = tid / kWave, l = tid % kWave;
@@ -175,20 +209,16 @@ __global__ __launch_bounds__(kThreads) void row_gemm_kernel(RowGemmArgs g) {
       bf[j][s] = g.b[(4 * s + l / 16) * g.b_rs + (16 * (wave + 4 * j) + l % 16) * g.b_cs];
   const int64_t n_tiles = (g.E + kRowTile - 1) / kRowTile;
   // the next tile's rows are loaded while this tile is multiplied
-  RowRegs<K1> x1r;
-  RowRegs<(K2 > 0 ? K2 : 4)> x2r;
+  RowRegs<K> xr;
   auto load = [&](int64_t t) {
     const int64_t r0 = t * kRowTile;
-    const int rows = int(g.E - r0 < kRowTile ? g.E - r0 : kRowTile);
-    x1r.load(g.x1, r0, rows, tid);
-    if constexpr (K2 > 0) x2r.load(g.x2, r0, rows, tid);
+    xr.load(g.x, r0, int(g.E - r0 < kRowTile ? g.E - r0 : kRowTile), tid);
   };
   if (int64_t(blockIdx.x) < n_tiles) load(blockIdx.x);
   for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     const int64_t r0 = t * kRowTile;
     const int rows = int(g.E - r0 < kRowTile ? g.E - r0 : kRowTile);
-    x1r.template put<PRO>(xs, XS, 0, tid);
-    if constexpr (K2 > 0) x2r.template put<kProNone>(xs, XS, K1, tid);
+    xr.template put<kProNone>(xs, XS, 0, tid);
     lds_sync<4>();
     if (t + gridDim.x < n_tiles) load(t + gridDim.x);
     f32x4 acc[kRowTile / 16][NJ];
@@ -216,40 +246,265 @@ __global__ __launch_bounds__(kThreads) void row_gemm_kernel(RowGemmArgs g) {
     lds_sync<4>();
     // epilogue by whole rows: float4 f = tid + 256 i is row f / (N / 4), columns 4 (f % (N / 4)) ..
     float4 dv[OPER];
-    if constexpr (EPI != kEpiStore) {
+    if constexpr (EPI == kEpiAdd) {
 #pragma unroll
       for (int i = 0; i < OPER; ++i) {
         const int f = tid + kThreads * i, row = f / (N / 4), col = 4 * (f % (N / 4));
         dv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < rows && (EPI != kEpiSplitAdd || col < N1)) {
-          const int64_t e = r0 + row;
-          dv[i] = *reinterpret_cast<const float4 *>(g.d + e * (EPI == kEpiSplitAdd ? N1 : N) + col);
-        }
+        if (row < rows) dv[i] = *reinterpret_cast<const float4 *>(g.d + (r0 + row) * N + col);
       }
     }
 #pragma unroll
     for (int i = 0; i < OPER; ++i) {
       const int f = tid + kThreads * i, row = f / (N / 4), col = 4 * (f % (N / 4));
       if (row >= rows) continue;
-      const int64_t e = r0 + row;
       float4 v = *reinterpret_cast<const float4 *>(xs + row * OS + col);
       if constexpr (EPI == kEpiAdd) {
         v.x += dv[i].x; v.y += dv[i].y; v.z += dv[i].z; v.w += dv[i].w;
-      } else if constexpr (EPI == kEpiSiluGrad) {
-        v.x *= silu_grad(dv[i].x); v.y *= silu_grad(dv[i].y); v.z *= silu_grad(dv[i].z); v.w *= silu_grad(dv[i].w);
       }
-      if constexpr (EPI == kEpiSplitAdd) {
-        if (col < N1) {
-          v.x += dv[i].x; v.y += dv[i].y; v.z += dv[i].z; v.w += dv[i].w;
-          *reinterpret_cast<float4 *>(g.c + e * N1 + col) = v;
-        } else {
-          *reinterpret_cast<float4 *>(g.c2 + e * (N - N1) + (col - N1)) = v;
-        }
-      } else {
-        *reinterpret_cast<float4 *>(g.c + e * N + col) = v;
-      }
+      *reinterpret_cast<float4 *>(g.c + (r0 + row) * N + col) = v;
     }
     lds_sync<4>();  // the products are read: the next X tile may land
+  }
+}
+
+// ---------------------------------------------------------- latent chain
+// The two dense steps of the latent update, or of its VJP, in one pass:
+//   forward   a = [h, s] B1,  c = h + SiLU(a) B2                (mid_out = a)
+//   backward  da = (dh' B2^T) * SiLU'(a),  [c | c2] = [dh', 0] + da B1^T  (mid_out = da)
+// X = [x1 | x2] is [E][K1], the middle [E][H], the result [E][N2].
+struct ChainArgs {
+  int64_t E;
+  const float *x1, *x2;    // X = [x1 | x2], [E][K1A] and [E][K1B]
+  const float *w1, *w2;    // W1[k][n] = w1[k * w1_rs + n * w1_cs], W2 likewise
+  int w1_rs, w1_cs, w2_rs, w2_cs;
+  const float *a;          // backward: the pre-activations [E][H]
+  float *mid_out;          // [E][H]
+  const float *add;        // [E][N2A], added to the first N2A columns of the result
+  float *c, *c2;           // result: columns < N2A to c, the rest to c2
+  int *ticket;             // set to zero for the mixing kernel launched after this one (may be null)
+};
+
+// B operands of CT = N / 16 column tiles of W [K][N] for 8 waves over a tile of
+// 64 rows (four row tiles): wave w owns column tiles w + 8 i whole, and of the
+// last four, if CT is not a multiple of eight, tile w % 4 for the row tiles
+// 2 (w / 4) and + 1.
+template <int K, int N>
+struct ChainWeights {
+  static constexpr int CT = N / 16, FULL = CT / 8, HALF = CT % 8 ? 1 : 0, OWN = FULL + HALF, KS = K / 32;
+  static_assert(K % 32 == 0 && N % 64 == 0, "whole column tiles");
+  Split8 w[OWN][KS];
+  static __device__ __forceinline__ int tile(int i, int wave) { return i < FULL ? wave + 8 * i : 8 * FULL + wave % 4; }
+  __device__ __forceinline__ void load(const float *__restrict__ p, int rs, int cs, int wave, int l) {
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          x[j] = p[(32 * ks + 8 * (l / 16) + j) * rs + (16 * tile(i, wave) + l % 16) * cs];
+        // odd steps are negated and summed apart: see mfma_split
+        w[i][ks] = split8(x, ks % 2 ? -kSplitScale : kSplitScale);
+      }
+  }
+};
+
+// The three bf16 parts of a [64][K] tile in LDS: part q of row r, column k at
+// (q 64 + r) (K + 8) + k.  The row stride, 4 (mod 64) words, puts the 16-byte
+// operand reads of 16 consecutive rows in distinct banks.
+template <int K>
+struct ChainPlanes {
+  static constexpr int STRIDE = K + 8, HALFS = 3 * 64 * STRIDE;  // HALFS: 16-bit elements
+  static __device__ __forceinline__ void put(uint16_t *p, int row, int col, float4 v) {
+    const float x[4] = {kSplitScale * v.x, kSplitScale * v.y, kSplitScale * v.z, kSplitScale * v.w};
+    uint32_t h[2], m[2], lo[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) split2(x[2 * i], x[2 * i + 1], h[i], m[i], lo[i]);
+    uint2 *d = reinterpret_cast<uint2 *>(p + row * STRIDE + col);
+    d[0] = make_uint2(h[0], h[1]);
+    d[64 * STRIDE / 4] = make_uint2(m[0], m[1]);
+    d[2 * 64 * STRIDE / 4] = make_uint2(lo[0], lo[1]);
+  }
+  static __device__ __forceinline__ Split8 get(const uint16_t *p, int row, int col) {
+    const bf16x8 *d = reinterpret_cast<const bf16x8 *>(p + row * STRIDE + col);
+    return {d[0], d[64 * STRIDE / 8], d[2 * 64 * STRIDE / 8]};
+  }
+};
+
+// out [64][OS] (fp32, LDS) = P W over the wave's column tiles; P are the planes
+// of a [64][K] tile.  A row tile whose sum is not finite is redone in fp32 with
+// P(row, k) and W(k, n) read through the callbacks.
+template <int K, int N, class PElem, class WElem>
+__device__ __forceinline__ void chain_gemm(const uint16_t *planes, const ChainWeights<K, N> &w, float *out, int OS,
+                                           int wave, int l, PElem p_elem, WElem w_elem) {
+  using W = ChainWeights<K, N>;
+#pragma unroll
+  for (int i = 0; i < W::OWN; ++i) {
+    const int rts = i < W::FULL ? 4 : 2, rt0 = i < W::FULL ? 0 : 2 * (wave / 4), col = 16 * W::tile(i, wave) + l % 16;
+#pragma unroll
+    for (int q = 0; q < rts; ++q) {
+      __builtin_amdgcn_sched_barrier(0);  // one row tile's operands at a time
+      const int rt = rt0 + q;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f}, neg = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < W::KS; ++ks) {
+        f32x4 &d = ks % 2 ? neg : acc;
+        d = mfma_split(ChainPlanes<K>::get(planes, 16 * rt + l % 16, 32 * ks + 8 * (l / 16)), w.w[i][ks], d);
+      }
+      acc -= neg;
+      float bad = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bad = __builtin_fmaf(acc[r], 0.f, bad);
+      acc *= kSplitUnscale;
+      if (__any(bad != bad)) {
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        int lane = l;
+        asm volatile("" : "+v"(lane));  // keeps these addresses out of the loop's registers
+        const int n = 16 * W::tile(i, wave) + lane % 16;
+#pragma unroll 1
+        for (int k = lane / 16; k < K; k += 4) acc = mfma_16x16x4(p_elem(16 * rt + lane % 16, k), w_elem(k, n), acc);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(16 * rt + 4 * (l / 16) + r) * OS + col] = acc[r];
+    }
+  }
+}
+
+constexpr int kChainThreads = 512, kChainRows = 64;
+
+// One workgroup of 8 waves per compute unit over 64-row tiles; both weight
+// matrices stay in registers, split (mfma_split).  Per tile: the rows of X,
+// loaded one tile ahead, go to LDS as bf16 planes; first product to an fp32
+// tile; middle step by whole rows (SiLU or its gradient, mid_out written, the
+// middle's planes over those of X); second product; result written by whole
+// rows.  The middle never returns from memory, and the matrix instructions run
+// at the bf16 rate: at L = 64, H = 128 and 523,599 edges (0.67 and 0.94 GB)
+// two row GEMMs on the fp32 matrix cores took 362 us forward and 461 backward
+// in the same run, this 239 and 278 (2.8 and 3.4 TB/s; what is left is the
+// tile's serial phases, four barriers with one workgroup on a unit).
+template <int K1A, int K1B, int H, int N2, int N2A, bool BWD>
+__global__ __launch_bounds__(kChainThreads) void latent_chain_kernel(ChainArgs g) {
+  constexpr int K1 = K1A + K1B, T = kChainThreads, R = kChainRows;
+  constexpr int PH = ChainPlanes<K1>::HALFS > ChainPlanes<H>::HALFS ? ChainPlanes<K1>::HALFS : ChainPlanes<H>::HALFS;
+  constexpr int MS = H + 4, OS = N2 + 4;  // row strides of the fp32 tiles
+  __shared__ uint4 planes4[PH / 8];
+  __shared__ float4 mid4[R * MS / 4], out4[R * OS / 4];
+  uint16_t *planes = reinterpret_cast<uint16_t *>(planes4);
+  float *mid = reinterpret_cast<float *>(mid4), *out = reinterpret_cast<float *>(out4);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), l = tid % kWave;
+  if (g.ticket && blockIdx.x == 0 && tid == 0) *g.ticket = 0;
+  ChainWeights<K1, H> w1;
+  ChainWeights<H, N2> w2;
+  w1.load(g.w1, g.w1_rs, g.w1_cs, wave, l);
+  w2.load(g.w2, g.w2_rs, g.w2_cs, wave, l);
+  const int64_t n_tiles = (g.E + R - 1) / R;
+  // float4 f = tid + 512 i of a [64][W] tile: row f / (W / 4), columns 4 (f % (W / 4)) ..
+  constexpr int XP = R * K1 / 4 / T, MP = R * H / 4 / T, OP = R * N2 / 4 / T;
+  static_assert(R * K1A / 4 % T == 0 && R * K1B / 4 % T == 0, "whole sources per thread");
+  // The addend is on its way during the second product and the backward's a a
+  // tile ahead, unless the result is 192 wide, where registers run out.
+  constexpr bool EARLY = OP < 6;
+  float4 xv[XP], av[BWD ? MP : 1];
+  // the rows of tile t of an [E][width] tensor, as far as it has any (accesses
+  // past the range read zeros and are dropped); within it float4 f sits at byte 16 f
+  auto rows_of = [&](const float *p, int width, int64_t t) {
+    const int64_t left = g.E - t * R;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p + t * R * width), short(0),
+                                             int(left < R ? left : R) * width * 4, 0x00020000);
+  };
+  // (the whole offset goes in voff: the scalar offset is not part of the range check)
+  auto load4 = [&](__amdgpu_buffer_rsrc_t r, int voff) {
+    const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+    return make_float4(v.x, v.y, v.z, v.w);
+  };
+  auto store4 = [&](__amdgpu_buffer_rsrc_t r, int voff, float4 v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v.x, v.y, v.z, v.w}), r, voff, 0, 0);
+  };
+  auto load = [&](int64_t t) {
+    constexpr int A = R * K1A / 4 / T;
+    const auto r1 = rows_of(g.x1, K1A, t);
+#pragma unroll
+    for (int i = 0; i < A; ++i) xv[i] = load4(r1, 16 * (tid + T * i));
+    if constexpr (K1B > 0) {
+      const auto r2 = rows_of(g.x2, K1B, t);
+#pragma unroll
+      for (int i = A; i < XP; ++i) xv[i] = load4(r2, 16 * (tid + T * (i - A)));
+    }
+  };
+  auto load_a = [&](int64_t t) {
+    const auto r = rows_of(g.a, H, t);
+#pragma unroll
+    for (int i = 0; i < MP; ++i) av[i] = load4(r, 16 * (tid + T * i));
+  };
+  if (int64_t(blockIdx.x) < n_tiles) {
+    load(blockIdx.x);
+    if constexpr (BWD && EARLY) load_a(blockIdx.x);
+  }
+  for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    const int64_t r0 = t * R;
+    const int rows = int(g.E - r0 < R ? g.E - r0 : R);
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      constexpr int A = R * K1A / 4 / T;
+      const int f = tid + T * (i < A ? i : i - A), W4 = (i < A ? K1A : K1B) / 4;
+      ChainPlanes<K1>::put(planes, f / W4, (i < A ? 0 : K1A) + 4 * (f % W4), xv[i]);
+    }
+    lds_sync<8>();
+    if constexpr (BWD && !EARLY) load_a(t);
+    if (t + gridDim.x < n_tiles) load(t + gridDim.x);
+    chain_gemm<K1, H>(planes, w1, mid, MS, wave, l,
+                      [&](int row, int k) {
+                        if (row >= rows) return 0.f;
+                        return k < K1A ? g.x1[(r0 + row) * K1A + k] : g.x2[(r0 + row) * K1B + (k - K1A)];
+                      },
+                      [&](int k, int n) { return g.w1[k * g.w1_rs + n * g.w1_cs]; });
+    lds_sync<8>();  // the first product is there, the planes of X have been read
+    const auto rm = rows_of(g.mid_out, H, t);
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      const int f = tid + T * i, row = f / (H / 4), col = 4 * (f % (H / 4));
+      float4 *m = reinterpret_cast<float4 *>(mid + row * MS + col);
+      float4 v = *m, keep;
+      if constexpr (BWD) {
+        v.x *= silu_grad(av[i].x); v.y *= silu_grad(av[i].y); v.z *= silu_grad(av[i].z); v.w *= silu_grad(av[i].w);
+        keep = v;
+      } else {
+        keep = v;
+        v.x = silu(v.x); v.y = silu(v.y); v.z = silu(v.z); v.w = silu(v.w);
+      }
+      store4(rm, 16 * (tid + T * i), keep);
+      *m = v;  // for a product that has to be redone in fp32
+      ChainPlanes<H>::put(planes, row, col, v);
+    }
+    if constexpr (BWD && EARLY) {
+      if (t + gridDim.x < n_tiles) load_a(t + gridDim.x);
+    }
+    float4 dv[OP];
+    auto load_add = [&] {
+      const auto r = rows_of(g.add, N2A, t);
+#pragma unroll
+      for (int i = 0; i < OP; ++i) {
+        const int f = tid + T * i, row = f / (N2 / 4), col = 4 * (f % (N2 / 4));
+        dv[i] = load4(r, col < N2A ? 4 * (row * N2A + col) : 4 * R * N2A);
+      }
+    };
+    if constexpr (EARLY) load_add();
+    lds_sync<8>();
+    chain_gemm<H, N2>(planes, w2, out, OS, wave, l, [&](int row, int k) { return mid[row * MS + k]; },
+                      [&](int k, int n) { return g.w2[k * g.w2_rs + n * g.w2_cs]; });
+    if constexpr (!EARLY) load_add();
+    lds_sync<8>();  // the result is there, the planes are free for the next tile
+    const auto rc = rows_of(g.c, N2A, t), rc2 = rows_of(N2 > N2A ? g.c2 : g.c, N2 > N2A ? N2 - N2A : N2A, t);
+#pragma unroll
+    for (int i = 0; i < OP; ++i) {
+      const int f = tid + T * i, row = f / (N2 / 4), col = 4 * (f % (N2 / 4));
+      const float4 p = *reinterpret_cast<const float4 *>(out + row * OS + col);
+      const float4 v = make_float4(p.x + dv[i].x, p.y + dv[i].y, p.z + dv[i].z, p.w + dv[i].w);
+      if (N2 == N2A || col < N2A) store4(rc, 4 * (row * N2A + col), v);
+      else store4(rc2, 4 * (row * (N2 - N2A) + col - N2A), v);
+    }
   }
 }
 
@@ -364,49 +619,6 @@ __device__ __forceinline__ void component_column(int k, int ne_tile, int &col0, 
     if (i == c) { o = X::off(i); d = X::dim(i); }
   col0 = ne_tile * o + (k - o);
   dim = d;
-}
-
-// fp32 products on the bf16 matrix cores.  x = h + m + l with h = bf16(x),
-// m = bf16(x - h), l = x - h - m: 8 significant bits each, rounded to nearest,
-// so the three hold all 24 bits of x exactly (both subtractions are exact).
-// Of the nine products of two split operands the six of weight 2^-16 and more
-// are summed (in fp32, by the matrix core), the small ones first; the three
-// dropped are below 2^-26 of the product, a quarter of the rounding of one
-// fp32 product.  The matrix core takes bf16 subnormals as zero, so both
-// operands are scaled by kSplitScale first: the smallest part of any fp32
-// value, 2^-149, is then a normal number.  The sum comes back through
-// kSplitUnscale; what overflows for the scale (or is infinite to begin with)
-// leaves a sum that is not finite, and the caller redoes it in fp32.
-constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
-
-struct Split8 {
-  bf16x8 h, m, l;
-};
-
-__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 h, m, l;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x2 v = {kSplitScale * x[2 * i], kSplitScale * x[2 * i + 1]};
-    const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-    const f32x2 r = {v.x - __builtin_bit_cast(float, hb << 16), v.y - __builtin_bit_cast(float, hb & 0xffff0000u)};
-    const uint32_t mb = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
-    const f32x2 q = {r.x - __builtin_bit_cast(float, mb << 16), r.y - __builtin_bit_cast(float, mb & 0xffff0000u)};
-    h[i] = hb;
-    m[i] = mb;
-    l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, bf16x2));
-  }
-  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
-}
-
-__device__ __forceinline__ f32x4 mfma_split(const Split8 &a, const Split8 &b, f32x4 c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b.h, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.l, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.m, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.m, b.h, c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.m, c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, b.h, c, 0, 0, 0);
 }
 
 // Column stride (floats): 68 = 4 (mod 64), so the 16-byte accesses of one
@@ -1025,13 +1237,21 @@ template <int L, int H>
 struct DenseOps {
   static constexpr int U = kU;
   // one workgroup per slot the GPU holds at once: each loads its B operands once
-  template <int K1, int K2, int N, int N1, int PRO, int EPI>
+  template <int K, int N, int EPI>
   static void row(hipStream_t s, const RowGemmArgs &g) {
     if (g.E == 0) return;
     static const int64_t slots =
-        resident_groups(reinterpret_cast<const void *>(&row_gemm_kernel<K1, K2, N, N1, PRO, EPI>), kThreads);
+        resident_groups(reinterpret_cast<const void *>(&row_gemm_kernel<K, N, EPI>), kThreads);
     const unsigned G = unsigned(std::min<int64_t>(cdiv(g.E, kRowTile), slots));
-    hipLaunchKernelGGL((row_gemm_kernel<K1, K2, N, N1, PRO, EPI>), dim3(G), dim3(kThreads), 0, s, g);
+    hipLaunchKernelGGL((row_gemm_kernel<K, N, EPI>), dim3(G), dim3(kThreads), 0, s, g);
+  }
+  template <int K1A, int K1B, int N2, int N2A, bool BWD>
+  static void chain(hipStream_t s, const ChainArgs &g) {
+    if (g.E == 0) return;
+    static const int64_t slots = resident_groups(
+        reinterpret_cast<const void *>(&latent_chain_kernel<K1A, K1B, H, N2, N2A, BWD>), kChainThreads);
+    const unsigned G = unsigned(std::min<int64_t>(cdiv(g.E, kChainRows), slots));
+    hipLaunchKernelGGL((latent_chain_kernel<K1A, K1B, H, N2, N2A, BWD>), dim3(G), dim3(kChainThreads), 0, s, g);
   }
   template <int M1, int M2, int N, int PRO>
   static void reduce(hipStream_t s, int64_t E, const float *p1, const float *p2, const float *q, float *part,
@@ -1045,19 +1265,17 @@ struct DenseOps {
 
   // w = h A;  a = [h, s] B1 (after the mixing has written s);  h' = h + SiLU(a) B2
   static void embed_weights(hipStream_t s, int64_t E, const float *h, const float *A, float *w, int *ticket) {
-    row<L, 0, U, 0, kProNone, kEpiStore>(s, {E, h, nullptr, A, U, 1, nullptr, w, nullptr, ticket});
+    row<L, U, kEpiStore>(s, {E, h, A, U, 1, nullptr, w, ticket});
   }
   static void latent(hipStream_t s, int64_t E, const float *h, const float *sv, const float *B1, const float *B2,
                      float *a, float *h_out) {
-    row<L, U, H, 0, kProNone, kEpiStore>(s, {E, h, sv, B1, H, 1, nullptr, a, nullptr, nullptr});
-    row<H, 0, L, 0, kProSilu, kEpiAdd>(s, {E, a, nullptr, B2, L, 1, h, h_out, nullptr, nullptr});
+    chain<L, U, L, L, false>(s, {E, h, sv, B1, B2, H, 1, L, 1, nullptr, a, h, h_out, nullptr, nullptr});
   }
   // da = (dh' B2^T) * SiLU'(a);  [dhm | ds] = [dh', 0] + da B1^T;  dB2, dB1
   static void latent_vjp(hipStream_t s, int64_t E, const float *h, const float *sv, const float *a,
                          const float *B1, const float *B2, const float *dh_out, float *da, float *dhm, float *ds,
                          float *part, float *dB1, float *dB2, int *ticket) {
-    row<L, 0, H, 0, kProNone, kEpiSiluGrad>(s, {E, dh_out, nullptr, B2, 1, L, a, da, nullptr, ticket});
-    row<H, 0, L + U, L, kProNone, kEpiSplitAdd>(s, {E, da, nullptr, B1, 1, H, dh_out, dhm, ds, nullptr});
+    chain<L, 0, L + U, L, true>(s, {E, dh_out, nullptr, B2, B1, 1, L, 1, H, a, da, dh_out, dhm, ds, ticket});
     reduce<H, 0, L, kProSilu>(s, E, a, nullptr, dh_out, part, dB2);
     reduce<L, U, H, kProNone>(s, E, h, sv, da, part, dB1);
   }
@@ -1065,7 +1283,7 @@ struct DenseOps {
   static void embed_vjp(hipStream_t s, int64_t E, const float *h, const float *A, const float *dw, const float *dhm,
                         float *part, float *dA, float *dh) {
     reduce<L, 0, U, kProNone>(s, E, h, nullptr, dw, part, dA);
-    row<U, 0, L, 0, kProNone, kEpiAdd>(s, {E, dw, nullptr, A, 1, U, dhm, dh, nullptr, nullptr});
+    row<U, L, kEpiAdd>(s, {E, dw, A, 1, U, dhm, dh, nullptr});
   }
 };
 

@@ -432,3 +432,50 @@ def test_layer_mixing_special_values(at, lmax, full):
     assert int(ok.sum()) > ok.numel() // 2
     # 64 partial sums may each be off by half the smallest subnormal step as well
     assert bool(((dT - ref).abs() <= MIX_TOL * mag + 64 * 2.0 ** -150)[ok].all())
+
+
+@pytest.mark.parametrize("L,H", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_layer_latent_special_values(at, L, H):
+    """Infinities, NaN, values next to the largest float and subnormal ones go through the latent
+    update's VJP as through fp32 products: da = (dh' B2^T) SiLU'(a) and ds = da B1^T (scalar columns),
+    in the workspace behind dT."""
+    plan, E = _plan(at, 1, False), 131
+    row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(1, False, L, H, [70, 61], seed=L + H)
+    dh_out[3, 5], dh_out[70, L - 1], dh_out[130, 0], dh_out[64, 9] = np.inf, -np.inf, np.nan, 3.4e38
+    dh_out[10] *= np.float32(2.0 ** -128)
+    dh_out[100] *= np.float32(2.0 ** -120)
+    dh_out[30] *= np.float32(1e30)
+    prm["B2"][7] = 0.0
+    wd = {k: _t(v) for k, v in prm.items()}
+    args = (plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+    _, _, saved = at.allegro_layer_forward(*args)
+    work = torch.empty(at.allegro_layer_buffers(plan, L, H, 2, E)[1], dtype=torch.uint8, device=DEV)
+    at.allegro_layer_backward(*args, saved, _t(dh_out), _t(dV_out), workspace=work)
+    up = lambda n: (4 * n + 255) // 256 * 256  # noqa: E731
+    a0 = up(E * 64) + up(2 * 64 * plan.d2) + up(E * 64 * plan.d1) + up(E * 64)
+    a = saved[a0:a0 + 4 * E * H].view(torch.float32).reshape(E, H).double()
+    d0 = up(E * 64 * plan.d1)
+    da = work[d0:d0 + 4 * E * H].view(torch.float32).reshape(E, H)
+    s0 = d0 + up(E * H) + up(E * L)
+    ds = work[s0:s0 + 4 * E * 64].view(torch.float32).reshape(E, 64)
+    g, b2 = _t(dh_out).double(), wd["B2"].double()
+    sg = torch.sigmoid(a)
+    slope = sg * (1 + a * (1 - sg))
+    t, mag = g @ b2.t().contiguous(), g.abs() @ b2.abs().t().contiguous()
+    # a sum of L products (one rounding each, and the split), times SiLU' with a few roundings of its own
+    _same_or_within(da, t.float().double() * slope, (L + 2) * 2.0 ** -24 * mag * slope.abs()
+                    + 8 * 2.0 ** -24 * (1 + a.abs()) * t.abs() + L * 2.0 ** -149)
+    d, b1 = da.double(), wd["B1"][L:].double()
+    _same_or_within(ds, d @ b1.t().contiguous(), (H + 2) * 2.0 ** -24 * (d.abs() @ b1.abs().t().contiguous())
+                    + H * 2.0 ** -149)
+
+
+def _same_or_within(got, ref, bound):
+    r32 = ref.float()
+    # next to the largest float either side of the overflow is within the bound
+    near = (ref.abs() > 3.0e38) & (ref.abs() < 4.0e38)
+    assert torch.equal(torch.isnan(got)[~near], torch.isnan(r32)[~near])
+    assert torch.equal(torch.isinf(got)[~near], torch.isinf(r32)[~near])
+    ok = torch.isfinite(r32) & ~near
+    assert int(ok.sum()) > ok.numel() // 2
+    assert bool(((got - ref).abs() <= bound)[ok].all())
