@@ -9,16 +9,17 @@
 //     split between the two channel halves.
 //   * The center's slabs (64 consecutive [U][d1] rows, contiguous in HBM) are
 //     dealt to its waves; each slab moves through an LDS tile with 16-byte
-//     coalesced accesses and each lane then works on its own row.  (The forward
-//     at lmax <= 2, which has no sums over edges, deals the slabs of the whole
-//     edge list instead and looks up each edge's center.)
-//   * Direct kernels (forward at lmax <= 2, inference backward at every
+//     coalesced accesses and each lane then works on its own row.  (The direct
+//     forward, which has no sums over edges, deals the slabs of the whole edge
+//     list instead and looks up each edge's center.)
+//   * Direct kernels (forward, inference backward at every
 //     lmax, training backward at lmax <= 2): path weights W[:, u] and
 //     env[n, u, :] are loaded once per center into VGPRs and the contraction
 //     runs in registers with the coupling coefficients as instruction literals
 //     (generated cores, tp_cores.inc).
-//   * Per-center matrices at lmax 3: the forward as out = M x with M built
-//     once per center, its rows split over 8 waves (generated TPMFwd); the
+//   * Per-center matrices at lmax 3: the forward (where a center has the edges
+//     to pay for it, else direct) as out = M x with M built once per center,
+//     its rows split over 8 waves (generated TPMFwd); the
 //     training backward as grad_x = g M and the per-center products
 //     G = sum_e g^T x on the matrix cores (tp_mfma_bwd_kernel, lane tables
 //     TPMfmaTab), then the embedding VJP in a launch of its own.
@@ -412,7 +413,7 @@ struct SlabRegs {
   }
 };
 
-// out = TP(x, env) over the flat list of edges (lmax <= 2): a wave takes S
+// out = TP(x, env) over the flat list of edges: a wave takes S
 // consecutive slabs (with two channel halves, of its half), a workgroup four
 // waves' worth, and workgroups start in edge order.  The center of an edge is
 // found by search while its x slab is on the way.  Bound by HBM (and the path
@@ -1843,23 +1844,33 @@ void launch_env(dim3 grid, hipStream_t s, int64_t N, const int64_t *rp, const fl
   hipLaunchKernelGGL((env_embed_kernel<U, D2, DET>), grid, dim3(kWave * kEnvWaves), 0, s, N, rp, w, Y, env);
 }
 
+constexpr int64_t kFewMatrixCenters = 160;
+
 template <class Core, int U>
 void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env,
                 const float *pw, float *out) {
+  using L = Lanes<U>;
   if constexpr (Core::LMAX >= 3) {
-    hipLaunchKernelGGL((tp_matrix_kernel<Core, U, TPMFwd<Core::LMAX, Core::FULL>>), dim3(unsigned(N)),
-                       dim3(kMFwdThreads<Core>), 0, s, rp, x, env, pw, out);
-  } else {
-    using L = Lanes<U>;
-    auto launch = [&](auto slabs) {
-      constexpr int S = decltype(slabs)::value;
-      const int64_t waves = (E + S * L::G - 1) / (S * L::G) * L::CPL;
-      hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((waves + kFwdWaves - 1) / kFwdWaves)),
-                         dim3(kWave * kFwdWaves), 0, s, N, E, rp, x, env, pw, out);
-    };
-    if (E * L::CPL / L::G < kFwdPairSlabs) launch(std::integral_constant<int, 1>{});
-    else launch(std::integral_constant<int, 2>{});
+    // The per-center matrix pays once its construction is shared by enough
+    // edges, and needs a center per compute unit; else the edge list is taken
+    // flat.  Matrix / flat, us: natural parity, 11 edges a center (U = 32) 42 /
+    // 34, 20 (U = 32) 59 / 54, 50 (U = 64) 128 / 132; full parity (U = 64), 7.5
+    // edges 468 / 416, 20 edges 274 / 287; 100 centers of 37 edges 34 / 23, 150
+    // of 50 46 / 41, 250 of 50 53 / 65.
+    if (E >= (Core::FULL ? 12 : 32) * N && N >= kFewMatrixCenters) {
+      hipLaunchKernelGGL((tp_matrix_kernel<Core, U, TPMFwd<Core::LMAX, Core::FULL>>), dim3(unsigned(N)),
+                         dim3(kMFwdThreads<Core>), 0, s, rp, x, env, pw, out);
+      return;
+    }
   }
+  auto launch = [&](auto slabs) {
+    constexpr int S = decltype(slabs)::value;
+    const int64_t waves = (E + S * L::G - 1) / (S * L::G) * L::CPL;
+    hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((waves + kFwdWaves - 1) / kFwdWaves)),
+                       dim3(kWave * kFwdWaves), 0, s, N, E, rp, x, env, pw, out);
+  };
+  if (E * L::CPL / L::G < kFwdPairSlabs) launch(std::integral_constant<int, 1>{});
+  else launch(std::integral_constant<int, 2>{});
 }
 
 // Persistent grid of the matrix-core backward: the workgroups resident on the

@@ -681,19 +681,24 @@ def test_step_replays_in_a_hip_graph(at):
 
 # ------------------------------------------- launch rules of the direct kernels
 
-@pytest.mark.parametrize("lmax,U,n,n_edges", [
+@pytest.mark.parametrize("lmax,full,U,n,n_edges", [
     # 512 centers: 4 waves a center below 16 slabs per center on average, 8 below 24, then 16; the
     # forward takes two slabs a wave from 8192 slabs on
-    (1, 64, 512, 8191), (1, 64, 512, 8192), (1, 64, 512, 12287), (1, 64, 512, 12288), (1, 64, 511, 8193),
-    (2, 16, 600, 4097), (2, 32, 600, 1203), (2, 128, 520, 4097),
+    (1, False, 64, 512, 8191), (1, False, 64, 512, 8192), (1, False, 64, 512, 12287), (1, False, 64, 512, 12288),
+    (1, False, 64, 511, 8193), (2, True, 16, 600, 4097), (2, True, 32, 600, 1203), (2, True, 128, 520, 4097),
+    # lmax 3: the forward takes the per-center matrix from 32 edges a center on (12 with full parity) and
+    # 160 centers on, else the flat edge list
+    (3, False, 16, 160, 5119), (3, False, 16, 160, 5120), (3, False, 16, 159, 5120), (3, False, 128, 40, 130),
+    (3, True, 16, 160, 1919), (3, True, 16, 160, 1920), (3, True, 32, 159, 2001), (3, True, 64, 20, 161),
+    (3, True, 128, 9, 41),
 ])
-def test_launch_rules_parity(at, lmax, U, n, n_edges):
-    _note(f"[gpu] launch rules lmax={lmax} U={U} N={n} E={n_edges}")
+def test_launch_rules_parity(at, lmax, full, U, n, n_edges):
+    _note(f"[gpu] launch rules lmax={lmax} full={full} U={U} N={n} E={n_edges}")
     rng = np.random.default_rng(n_edges)
     degrees = np.bincount(rng.integers(0, n, n_edges), minlength=n)
-    data = _synthetic(lmax, lmax == 2, U, degrees, seed=n_edges)
-    gpu = _np(_run_gpu(at, _plan(at, lmax, U, lmax == 2), *data))
-    t, *ref = _oracle(lmax, lmax == 2, *data)
+    data = _synthetic(lmax, full, U, degrees, seed=n_edges)
+    gpu = _np(_run_gpu(at, _plan(at, lmax, U, full), *data))
+    t, *ref = _oracle(lmax, full, *data)
     _compare(t, gpu, ref, f"lmax{lmax} U{U} N{n} E{n_edges}")
 
 
