@@ -31,7 +31,7 @@
  * row-major fp32 device memory, 16-byte aligned, no aliasing between inputs
  * and outputs, asynchronous on `stream`, no allocation per call, negative
  * codes with allegro_last_error().  The dense contractions (steps 1, 4 and 6
- * and their gradients) run on the fp32 matrix cores; the tensor product and
+ * and their gradients) run in fp32 on the matrix cores; the tensor product and
  * the embedding run the kernels of allegro_tp.h.  Every reduction over edges
  * has a fixed order, so results are bit-identical run to run.
  */

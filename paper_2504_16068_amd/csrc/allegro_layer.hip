@@ -1,8 +1,9 @@
 // MI355X (gfx950) kernels and C ABI of one Allegro layer around the tensor
 // product.  What is computed is stated in include/allegro_layer.h.
 //
-// The dense contractions run on the fp32 matrix cores with
-// v_mfma_f32_16x16x4_f32: for one instruction lane l supplies A[l % 16][l / 16]
+// The dense contractions run in fp32 on the matrix cores: through split
+// operands on v_mfma_f32_16x16x32_bf16 (mfma_split) or with
+// v_mfma_f32_16x16x4_f32.  For one of the latter lane l supplies A[l % 16][l / 16]
 // and B[l / 16][l % 16], and accumulator register r of lane l holds
 // D[4 (l / 16) + r][l % 16].  Over the steps of a sum, lane group l / 16
 // either interleaves with the others (k = 4 s + l / 16) or owns a contiguous
