@@ -430,14 +430,15 @@ constexpr int64_t kFwdPairSlabs = 256 * 16 * 2;  // slabs from which a wave take
 
 template <class Core, int U, int S>
 __global__ __launch_bounds__(kWave * kFwdWaves) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::kFwdOccupancy)))
-void tp_forward_kernel(int64_t N, int64_t E, const int64_t *__restrict__ row_ptr, const float *__restrict__ x,
-                       const float *__restrict__ env, const float *__restrict__ path_w, float *__restrict__ out) {
+void tp_forward_kernel(int64_t N, int64_t E, int64_t first_wave, const int64_t *__restrict__ row_ptr,
+                       const float *__restrict__ x, const float *__restrict__ env, const float *__restrict__ path_w,
+                       float *__restrict__ out) {
   using L = Lanes<U>;
   constexpr int D1 = Core::D1, D2 = Core::D2;
   constexpr int TF4 = TileShape<D1>::SF4;  // one slab per tile
   __shared__ float4 tiles[kFwdWaves * TileShape<D1>::LF4];
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave), lane = threadIdx.x % kWave;
-  const int64_t gw = int64_t(blockIdx.x) * kFwdWaves + wave;  // of this launch's waves
+  const int64_t gw = first_wave + int64_t(blockIdx.x) * kFwdWaves + wave;
   const int t = int(gw % L::CPL), u = lane % L::LPE + t * kWave;
   const int64_t first = gw / L::CPL * (S * L::G);  // the wave's first edge
   float4 *tile = tiles + wave * TileShape<D1>::LF4;
@@ -1845,6 +1846,7 @@ void launch_env(dim3 grid, hipStream_t s, int64_t N, const int64_t *rp, const fl
 }
 
 constexpr int64_t kFewMatrixCenters = 160;
+constexpr int64_t kFwdLaunchWaves = int64_t(1) << 25;  // waves of one launch of the direct forward
 
 template <class Core, int U>
 void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env,
@@ -1866,8 +1868,12 @@ void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const fl
   auto launch = [&](auto slabs) {
     constexpr int S = decltype(slabs)::value;
     const int64_t waves = (E + S * L::G - 1) / (S * L::G) * L::CPL;
-    hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((waves + kFwdWaves - 1) / kFwdWaves)),
-                       dim3(kWave * kFwdWaves), 0, s, N, E, rp, x, env, pw, out);
+    // a launch takes fewer than 2^32 threads
+    for (int64_t w0 = 0; w0 < waves; w0 += kFwdLaunchWaves) {
+      const int64_t n = std::min(waves - w0, kFwdLaunchWaves);
+      hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((n + kFwdWaves - 1) / kFwdWaves)),
+                         dim3(kWave * kFwdWaves), 0, s, N, E, w0, rp, x, env, pw, out);
+    }
   };
   if (E * L::CPL / L::G < kFwdPairSlabs) launch(std::integral_constant<int, 1>{});
   else launch(std::integral_constant<int, 2>{});
