@@ -155,7 +155,7 @@ int allegro_tp_backward_workspace(const allegro_tp_plan *plan, int64_t N, size_t
  * channel group and sums the contributions of the centers it visits, in
  * order, into one channel-major workspace row of its own (R rounds of U rows
  * of n_paths floats, R = its wave count over U / channels per wave: 16 on a
- * 256-compute-unit MI355X at U = 128); one launch sums the R rounds in order.
+ * 256-compute-unit MI355X at U = 128); one launch sums the R rounds in a fixed order.
  * The grid is fixed per device, so the result is bit-identical run to run on
  * one device.  The other four gradients
  * equal allegro_tp_backward's up to fp32 rounding (the two split the work
@@ -191,7 +191,7 @@ int allegro_tp_backward_train(const allegro_tp_plan *plan, int64_t N, int64_t E,
  * bit for bit.  At lmax < 3 the centers are processed in chunks of
  * C = floor(16 Mi / (n_paths * U)) - 384 centers (8,354 at lmax 2, U = 64);
  * each chunk's per-center rows are summed in a fixed order into one row, and
- * the chunk rows in order into grad_path_w, so the result is deterministic and
+ * the chunk rows in a fixed order into grad_path_w, so the result is deterministic and
  * equals allegro_tp_backward_train's up to fp32 rounding order (grad_x,
  * grad_env, grad_w and grad_Y are bit-identical to it); at most 256 chunks:
  * N > 256 * C returns ALLEGRO_E_INVALID before any launch.  Every call on one GPU shares that GPU's array and overwrites it, so
