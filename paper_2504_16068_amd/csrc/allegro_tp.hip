@@ -441,6 +441,11 @@ void tp_forward_kernel(int64_t N, int64_t E, int64_t first_wave, const int64_t *
   const int64_t gw = first_wave + int64_t(blockIdx.x) * kFwdWaves + wave;
   const int t = int(gw % L::CPL), u = lane % L::LPE + t * kWave;
   const int64_t first = gw / L::CPL * (S * L::G);  // the wave's first edge
+  // As in the per-center kernels only the edges of the centers at hand count:
+  // row_ptr may be a range of a longer one (its values edge indices all the
+  // same), and x and out may have rows to spare.
+  const int64_t E0 = row_ptr[0], E1 = row_ptr[N] < E ? row_ptr[N] : E;
+  if (first >= E1 || first + S * L::G <= E0) return;
   float4 *tile = tiles + wave * TileShape<D1>::LF4;
   float *tile_f = reinterpret_cast<float *>(tile);
   // every slab's loads first: the search, the weights and env arrive under them
@@ -472,7 +477,7 @@ void tp_forward_kernel(int64_t N, int64_t E, int64_t first_wave, const int64_t *
     const int64_t eb = first + k * L::G;  // the slab's first edge
     xs[k].put(tile, lane);
     lds_sync<1>();
-    if (row_valid<U>(eb, E, 0, lane)) {
+    if (row_valid<U>(eb, E1, 0, lane)) {
       float *row = tile_f + lane * TileShape<D1>::RS;
       float xr[D1], orow[D1];
 #pragma unroll
@@ -482,7 +487,15 @@ void tp_forward_kernel(int64_t N, int64_t E, int64_t first_wave, const int64_t *
       for (int i = 0; i < D1; ++i) row[i] = orow[i];
     }
     lds_sync<1>();
-    if (eb < E) tile_store<U, D1, TF4>(out, tile, eb, E, 0, 1, t, lane);
+    if (eb >= E0 && eb < E1) {
+      tile_store<U, D1, TF4>(out, tile, eb, E1, 0, 1, t, lane);
+    } else if (L::G > 1 && eb < E1) {  // the slab in which the first center's edges begin
+      for (int f = lane; f < TF4; f += kWave) {
+        const int64_t e = eb + f / (U * D1 / 4);
+        if (e >= E0 && e < E1)
+          store_stream(tile[TileShape<D1>::pos(f)], reinterpret_cast<float4 *>(out) + eb * (U * D1 / 4) + f);
+      }
+    }
     lds_sync<1>();
   }
 }

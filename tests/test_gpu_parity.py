@@ -720,3 +720,41 @@ def test_forward_finds_centers_among_empty_ones(at, U):
         assert block_rel_err(env[at_], renv, t.env_slices) <= FWD_TOL and np.count_nonzero(env) == np.count_nonzero(
             env[at_])
         assert block_rel_err(out, t.forward(dense, x, renv, pw), t.x_slices) <= FWD_TOL
+
+
+@pytest.mark.parametrize("lmax,full,U", [(1, False, 16), (2, True, 16), (2, True, 32), (2, False, 64), (2, True, 128),
+                                         (3, False, 32), (3, True, 64), (3, True, 128)])
+def test_calls_over_a_range_of_centers_leave_the_other_edges_alone(at, lmax, full, U):
+    """row_ptr[a:b + 1] with the env rows of centers a..b-1 computes those centers' edges within the whole
+    x and out, and x and out may have more rows than row_ptr says: no other row is written."""
+    _note(f"[gpu] center ranges lmax={lmax} full={full} U={U}")
+    degrees = [3, 0, 5, 1, 0, 2, 7, 66, 1, 0, 4, 129, 2, 0]
+    row_ptr, x, w, y, pw, g = _synthetic(lmax, full, U, degrees, seed=U)
+    spare = 37
+    plan, E = _plan(at, lmax, U, full), int(row_ptr[-1])
+
+    def padded(a, value):
+        return torch.cat([_t(a), torch.full((spare,) + a.shape[1:], value, device=DEV)])
+
+    t, renv, rout, rgrads = _oracle(lmax, full, row_ptr, x, w, y, pw, g)
+    rp, pwd = _t(row_ptr), _t(pw)
+    xd, wd, yd, gd = (padded(a, np.nan) for a in (x, w, y, g))
+    out = torch.full_like(xd, 7.0)
+    env = torch.empty((len(degrees), U, plan.d2), device=DEV)
+    grads = [torch.full_like(xd, 7.0), torch.empty_like(env), torch.full_like(wd, 7.0), torch.full_like(yd, 7.0)]
+    done = 0
+    for a, b in ((0, 4), (4, 5), (5, 8), (8, 14)):
+        sub = rp[a:b + 1].clone()
+        env[a:b] = at.allegro_env_embed(plan, sub, wd, yd)
+        at.allegro_tp_forward(plan, sub, xd, env[a:b].clone(), pwd, out=out)
+        genv = torch.empty((b - a, U, plan.d2), device=DEV)
+        at.allegro_tp_backward(plan, sub, xd, env[a:b].clone(), pwd, gd, wd, yd,
+                               outs=(grads[0], genv, grads[2], grads[3]))
+        grads[1][a:b] = genv
+        done = int(row_ptr[b])
+        for o in (out, grads[0], grads[2], grads[3]):
+            assert bool((o[done:] == 7.0).all()), (a, b)
+    assert done == E
+    gpu = (env.cpu().numpy(), out[:E].cpu().numpy(),
+           tuple((o if o is grads[1] else o[:E]).cpu().numpy() for o in grads))
+    _compare(t, gpu, (renv, rout, rgrads), f"center ranges lmax{lmax} U{U}")
