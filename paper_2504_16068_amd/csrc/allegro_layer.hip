@@ -91,11 +91,13 @@ struct XIrreps {
 // leaves a sum that is not finite, and the caller redoes it in fp32.
 //
 // The matrix core rounds its bf16 sums down, not to nearest: the values carry a
-// mean error of about -1e-8 of their size.  Where a sum over every edge follows
-// directly (latent_chain_kernel, then dB1 and dB2) that shows: dB1's error rose
-// from 5.1e-7 to 5.6e-7.  There half of a sum's steps are taken with negated
-// weights into an accumulator of their own and subtracted at the end, where the
-// two means cancel.
+// mean error of about -1e-8 of their size, and every result here is later summed
+// over edges (dB1's error rose from 5.1e-7 to 5.6e-7), where the mean grows with
+// the count and the rest with its root.  So half of the sums are formed with the
+// opposite sign.  latent_chain_kernel takes half of a sum's steps with negated
+// weights into an accumulator of their own and subtracts it at the end;
+// mix_kernel negates every other column, which are, as irreps have odd
+// dimensions, every other edge of each component.
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
 struct Split8 {
@@ -686,6 +688,15 @@ struct MixTile {
   static_assert(BUSY <= kMixComputeWaves, "compute waves");
 };
 
+// v, negated in odd columns.  A column's reads start at a multiple of 4 floats
+// whose bit 2 is the column's lowest (kMixCS = 68, the lane group adds 16): made
+// at each use from the offset at hand, since a register kept for it would spill.
+__device__ __forceinline__ float column_sign(int rd, float v) {
+  float r;
+  asm volatile("v_lshl_or_b32 %0, %1, 29, %2" : "=v"(r) : "v"(rd), "s"(v));
+  return r;
+}
+
 template <class X, bool BWD, int LA, int LB>
 __device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_tiles, const float *__restrict__ mix,
                                                   float *lds, int *order, int *__restrict__ ticket) {
@@ -695,6 +706,7 @@ __device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_til
   int l = threadIdx.x % kWave;
   asm volatile("" : "+v"(l));  // nothing derived from it is shared, and held, across the pairs' code
   const int g = l / 16, q = l % 16;
+  const float scale = q % 2 ? -kSplitScale : kSplitScale;  // odd columns have the opposite sign: see mfma_split
   // The irreps, and the lane's LDS offsets in a buffer of its reads (rd) and
   // writes (wr) in their first column tile; opaque, so that the tiles' addresses
   // are immediate offsets from these and not a register each.
@@ -745,7 +757,7 @@ __device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_til
       for (int ks = 0; ks < 2; ++ks) {
         const float4 u = bp[2 * ks], v = bp[2 * ks + 1];
         const float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-        const Split8 B = split8(x);
+        const Split8 B = split8(x, scale);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) acc[i][rt] = mfma_split(A[s][rt][ks], B, acc[i][rt]);
       }
@@ -776,7 +788,7 @@ __device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_til
           for (int k = 0; k < 16; ++k)
             a = mfma_16x16x4(elem(cs[s], 16 * (RT * rs + rt) + qo, 16 * go + k),
                              b[rd[s] + 16 * ct * CS + k], a);
-          acc[i][rt] = a;
+          acc[i][rt] = a * column_sign(rd[s], 1.f);
         }
       });
     }
@@ -787,7 +799,7 @@ __device__ __forceinline__ void mix_compute_waves(int par, int rs, int64_t n_til
       if (16 * ct + q < nq) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          f32x4 v = acc[i][rt];
+          f32x4 v = acc[i][rt] * column_sign(rd[s], 1.f);
           // the 0e irrep also has the gradient of s: [edge][position] behind the tile buffers
           if (BWD && LA == 0 && s == 0 && par == 0)
             v += *reinterpret_cast<const f32x4 *>(lds + 2 * M::BUF + (16 * ct + q) * U + 16 * (RT * rs + rt) + 4 * g);

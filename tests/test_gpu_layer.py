@@ -405,6 +405,36 @@ def test_layer_mixing_tiles(at, lmax, full, tile):
         assert bool(((dT - ref).abs() <= MIX_TOL * mag).all())
 
 
+@pytest.mark.parametrize("lmax,full,E", [(1, False, 40001), (1, True, 20001), (2, False, 20001), (2, True, 10001),
+                                         (3, False, 10001), (3, True, 6001)])
+def test_layer_mixing_errors_have_no_mean(at, lmax, full, E):
+    """Mixed values are summed over edges afterwards (grad_env, dW, dA; the next layer's embedding), so their
+    errors must not lean downwards whatever the value: over values of either sign their mean, in all and for
+    each component, is what independent errors of the measured size give (six times their size over the root
+    of their number)."""
+    _note(f"[gpu] mixing mean error lmax={lmax} full={full} E={E}")
+    plan, L, H = _plan(at, lmax, full), 64, 64
+    deg = np.full((E + 49) // 50, 50)
+    deg[-1] -= deg.sum() - E
+    row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(lmax, full, L, H, deg, seed=E)
+    wd = {k: _t(v) for k, v in prm.items()}
+    dV = _t(dV_out)
+    args = (plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+    _, V_out, saved = at.allegro_layer_forward(*args)
+    work = torch.empty(at.allegro_layer_buffers(plan, L, H, len(deg), E)[1], dtype=torch.uint8, device=DEV)
+    at.allegro_layer_backward(*args, saved, torch.zeros_like(_t(dh_out)), dV, workspace=work)
+    T, _ = _saved_product(saved, plan, len(deg), E)
+    dT = work[:4 * E * 64 * plan.d1].view(torch.float32).reshape(E, 64, plan.d1)
+    for name, got, src, transposed in (("V_out", V_out, T, False), ("dT", dT, dV, True)):
+        ref, mag = _mixed(plan, wd["Mix"], src, transposed)
+        err = (got - ref) / mag
+        mean, rms = float(err.mean()), float(err.square().mean().sqrt())
+        by_component = float(err.mean(dim=(0, 1)).abs().max())
+        _note(f"  {name}: mean {mean:.2e}, largest of a component {by_component:.2e}, rms {rms:.2e}")
+        assert abs(mean) <= 6 * rms / err.numel() ** 0.5
+        assert by_component <= 6 * rms / (E * 64) ** 0.5
+
+
 @pytest.mark.parametrize("lmax,full", [(1, False), (1, True), (2, False), (2, True), (3, False), (3, True)])
 def test_layer_mixing_special_values(at, lmax, full):
     """Infinities, NaN, values next to the largest float and subnormal ones go through the mixing as
