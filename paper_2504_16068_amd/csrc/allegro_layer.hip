@@ -1184,7 +1184,7 @@ struct SavedLayout {
   size_t w, env, T, s, a, total;
 };
 struct WorkLayout {
-  size_t dT, da, dhm, ds, dw, genv, tpws, red, mixp, ticket, total, tpws_bytes;
+  size_t dT, da, dhm, ds, dw, genv, tpws, red, mixp, total, tpws_bytes;
 };
 
 SavedLayout saved_layout(const Shape &z) {
@@ -1218,7 +1218,6 @@ WorkLayout work_layout(const allegro_tp_plan *plan, const Shape &z) {
   const size_t mn = std::max({size_t(z.L + z.U) * z.H, size_t(z.H) * z.L, size_t(z.L) * z.U});
   o.red = take(size_t(red_groups(z.E)) * mn * f);
   o.mixp = take(size_t(wgrad_groups(z.E)) * z.NX * z.U * z.U * f);
-  o.ticket = take(sizeof(int));
   o.total = at;
   return o;
 }
@@ -1507,7 +1506,7 @@ int allegro_layer_backward(const allegro_tp_plan *plan, int L, int H, int64_t N,
   float *dT = at<float>(workspace, wl.dT), *da = at<float>(workspace, wl.da), *dhm = at<float>(workspace, wl.dhm);
   float *ds = at<float>(workspace, wl.ds), *dw = at<float>(workspace, wl.dw), *genv = at<float>(workspace, wl.genv);
   float *red = at<float>(workspace, wl.red), *mixp = at<float>(workspace, wl.mixp);
-  int *ticket = at<int>(workspace, wl.ticket);
+  int *ticket = at<int>(workspace, wl.dw);  // in dw's region, which is written after the mixing
   dn.latent_vjp(s, E, h, sv, a, B1, B2, dh_out, da, dhm, ds, red, dB1, dB2, ticket);
   mx.backward(s, E, dV_out, T, Mix, ds, dT, mixp, dMix, ticket);
   if ((rc = after("allegro_layer_backward"))) return rc;

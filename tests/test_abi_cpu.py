@@ -58,6 +58,19 @@ def test_binding_argument_counts_match_headers():
             assert len(fn.argtypes) == n, (name, len(fn.argtypes), n)
 
 
+@pytest.mark.parametrize("lmax,full,L,H,n,e,saved,work", [
+    (1, False, 64, 64, 1, 1, 2816, 200704),
+    (2, True, 64, 128, 10, 100, 586240, 4260352),
+    (2, True, 128, 128, 7, 0, 16128, 1052928),
+    (3, True, 64, 128, 100, 3700, 34508800, 108106752),
+    (3, False, 128, 64, 5003, 206624, 1025511424, 1196052480),
+])
+def test_layer_buffer_sizes_stay(lmax, full, L, H, n, e, saved, work):
+    """A program may store the sizes and pass buffers of them later: a larger need would refuse those."""
+    plan = binding.allegro_tp_plan_create(lmax, 64, binding.ALLEGRO_FULL_PARITY if full else 0)
+    assert binding.allegro_layer_buffers(plan, L, H, n, e) == (saved, work)
+
+
 def test_layer_rejects_bad_arguments_before_any_launch():
     lib = binding.library()
     vp, sz = ctypes.c_void_p, ctypes.c_size_t
