@@ -942,11 +942,12 @@ struct BwdLds {
   static_assert(!WG || PC >= 1, "LDS too small for the path-weight partial sums");
 };
 
-// With WG the kernel also writes center n's path-weight gradient, summed over
-// its edges, to pw_part[n][p][u] (the first of the two reduction stages).
-template <class Core, int U, bool WG, int NW = TPWaves<Core, U>::bwd(WG)>
-__global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::bwd_occupancy(WG)))) void tp_backward_kernel(
-        const int64_t *__restrict__ row_ptr, const float *__restrict__ x, const float *__restrict__ env,
+// The backward of center n by the NW waves of a workgroup.  With WG it also
+// writes the center's path-weight gradient, summed over its edges, to
+// pw_part[n][p][u] (the first of the two reduction stages).
+template <class Core, int U, bool WG, int NW>
+__device__ __forceinline__ void backward_center(
+        int wave, int lane, int64_t n, int64_t e0, int64_t e1, float4 *smem, const float *__restrict__ x, const float *__restrict__ env,
         const float *__restrict__ path_w, const float *__restrict__ g, const float *__restrict__ w,
         const float *__restrict__ Y, float *__restrict__ grad_x, float *__restrict__ grad_env,
         float *__restrict__ grad_w, float *__restrict__ grad_Y, float *__restrict__ pw_part) {
@@ -954,12 +955,9 @@ __global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(Kern
   using B = BwdLds<Core, U, WG, NW>;
   constexpr int D2 = Core::D2, NP = Core::NP, WPT = NW / L::CPL, NT = NW * kWave;
   static_assert(NW % L::CPL == 0, "waves split evenly over the channel halves");
-  __shared__ float4 smem[(B::FLOATS + 3) / 4];
   float *lds = reinterpret_cast<float *>(smem);
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, grp = lane / L::LPE, ul = lane % L::LPE;
+  const int tid = wave * kWave + lane, grp = lane / L::LPE, ul = lane % L::LPE;
   const int t = wave / WPT;
-  const int64_t n = blockIdx.x;
-  const int64_t e0 = row_ptr[n], e1 = row_ptr[n + 1];
   const int64_t n_slabs = Slabs<U>::count(e1 - e0);
 
   // Pass 1 (lane <-> channel): grad_x per edge, partial sums per wave in registers.
@@ -1018,6 +1016,70 @@ __global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(Kern
   // Pass 2: the embedding's VJP through grad_env
   embedding_vjp<U, D2, NW, B::EB>(ge_l, lds + B::GE_PART + B::GE_ROW + wave * B::STAGE, e0, e1, wave, lane, w, Y,
                                   grad_w, grad_Y);
+}
+
+// One workgroup per center.  With fewer waves than the widest launch it leaves
+// centers of more than long_edges edges to tp_backward_long_kernel.
+template <class Core, int U, bool WG, int NW = TPWaves<Core, U>::bwd(WG)>
+__global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::bwd_occupancy(WG)))) void tp_backward_kernel(
+        int64_t long_edges, const int64_t *__restrict__ row_ptr, const float *__restrict__ x,
+        const float *__restrict__ env, const float *__restrict__ path_w, const float *__restrict__ g,
+        const float *__restrict__ w, const float *__restrict__ Y, float *__restrict__ grad_x,
+        float *__restrict__ grad_env, float *__restrict__ grad_w, float *__restrict__ grad_Y,
+        float *__restrict__ pw_part) {
+  __shared__ float4 smem[(BwdLds<Core, U, WG, NW>::FLOATS + 3) / 4];
+  const int64_t n = blockIdx.x, e0 = row_ptr[n], e1 = row_ptr[n + 1];
+  if constexpr (NW < TPWaves<Core, U>::bwd(WG)) {
+    if (e1 - e0 > long_edges) return;
+  }
+  backward_center<Core, U, WG, NW>(threadIdx.x / kWave, threadIdx.x % kWave, n, e0, e1, smem, x, env, path_w, g, w, Y, grad_x, grad_env, grad_w, grad_Y,
+                                   pw_part);
+}
+
+// The centers of more than long_edges edges that a launch with fewer waves per
+// center has left, with 16 waves each.  Workgroup b looks at centers b, b + G,
+// b + 2 G, .. (G workgroups), a thread each, and takes the long ones in order.
+// Bound by the latency of each center's slabs, as in the 16-wave launch.  One
+// workgroup per compute unit: 4 per unit take 8 us instead of 3 when nothing is long.
+template <class Core, int U>
+__global__ __launch_bounds__(kWave * 16) __attribute__((amdgpu_waves_per_eu(KernelTraits<Core>::bwd_occupancy(false)))) void tp_backward_long_kernel(
+        int64_t N, int64_t long_edges, const int64_t *__restrict__ row_ptr, const float *__restrict__ x,
+        const float *__restrict__ env, const float *__restrict__ path_w, const float *__restrict__ g,
+        const float *__restrict__ w, const float *__restrict__ Y, float *__restrict__ grad_x,
+        float *__restrict__ grad_env, float *__restrict__ grad_w, float *__restrict__ grad_Y) {
+  constexpr int NW = 16;
+  __shared__ float4 smem[(BwdLds<Core, U, false, NW>::FLOATS + 3) / 4];
+  __shared__ uint64_t found[NW];
+  const int64_t G = gridDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+  for (int64_t base = blockIdx.x; base < N; base += G * (kWave * NW)) {
+    const int64_t mine = base + int64_t(threadIdx.x) * G;
+    const int64_t at = mine < N ? mine : 0;
+    const uint64_t m = __ballot(mine < N && row_ptr[at + 1] - row_ptr[at] > long_edges);
+    if (threadIdx.x % kWave == 0) found[threadIdx.x / kWave] = m;
+    lds_sync<NW>();
+#pragma unroll 1
+    for (int k = 0; k < NW; ++k) {
+      const uint64_t f = found[k];
+      // (readfirstlane returns an int: through uint32_t, or bit 31 would spread)
+      uint64_t left = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(f))) |
+                      uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(f >> 32)))) << 32;
+#pragma unroll 1
+      while (left) {
+        const int64_t n = base + (k * kWave + __builtin_ctzll(left)) * G;
+        left &= left - 1;
+        // The lane's index is made anew, so that neither it nor what follows from
+        // it is kept from center to center: there are no registers for that.
+        int lane;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        lane &= kWave - 1;  // its range, which the compiler cannot see
+        backward_center<Core, U, false, NW>(wave, lane, n, row_ptr[n], row_ptr[n + 1], smem, x, env, path_w, g, w, Y,
+                                            grad_x, grad_env, grad_w, grad_Y, nullptr);
+        lds_sync<NW>();  // smem is free for the next center
+      }
+    }
+    lds_sync<NW>();  // found has been read
+  }
 }
 
 // ------------------------------------- backward at lmax 3 on the matrix cores
@@ -1934,7 +1996,11 @@ int64_t mfma_pw_rounds(int64_t N) {
   return int64_t(mfma_grid<FULL, U, true>(N)) * MfmaShape<FULL>::NW / (U / MfmaShape<FULL>::CPW);
 }
 
-constexpr int64_t kFewCenters = 512;  // centers below which one workgroup per compute unit is all there is
+// Slabs from which a center waits for tp_backward_long_kernel: with 48, graphs of many
+// such centers (1,100 centers, 80% empty, the others 50 edges at U = 64) took 124 us instead of 72,
+// since that kernel's share-out is fixed; with 128 a center costs at most 0.1 ms of tail.
+constexpr int kLongSlabs = 128;
+constexpr unsigned kLongGroups = 256;  // workgroups of that kernel
 
 template <class Core, int U, bool WG>
 void launch_bwd(dim3 grid, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env, const float *pw,
@@ -1952,21 +2018,34 @@ void launch_bwd(dim3 grid, int64_t E, hipStream_t s, const int64_t *rp, const fl
   } else {
     auto launch = [&](auto waves) {
       constexpr int NW = decltype(waves)::value;
-      hipLaunchKernelGGL((tp_backward_kernel<Core, U, WG, NW>), grid, dim3(kWave * NW), 0, s, rp, x, env, pw, g, w, Y,
-                         gx, genv, gw, gy, pw_part);
+      const int64_t long_edges = kLongSlabs * kWave / U;
+      hipLaunchKernelGGL((tp_backward_kernel<Core, U, WG, NW>), grid, dim3(kWave * NW), 0, s, long_edges, rp, x, env, pw,
+                         g, w, Y, gx, genv, gw, gy, pw_part);
+      if constexpr (NW < TPWaves<Core, U>::bwd(WG))
+        hipLaunchKernelGGL((tp_backward_long_kernel<Core, U>), dim3(std::min(grid.x, kLongGroups)), dim3(kWave * 16), 0, s,
+                           int64_t(grid.x), long_edges, rp, x, env, pw, g, w, Y, gx, genv, gw, gy);
     };
     constexpr int NW = TPWaves<Core, U>::bwd(WG);
     if constexpr (NW == 16) {
       // Waves a center's slabs cannot keep busy only hold their compute unit
-      // (one workgroup of 16 fits): with several centers per unit, fewer waves
-      // for fewer slabs per center.  Inference backward, 16 / 8 / 4 waves, us:
-      // 52 slabs (U = 64) 2720 / 2860 / 2910, 26 (U = 64) 486 / 422 / 434, 13
-      // (U = 64) 445 / 367 / 321, 13 (U = 16) 144 / 113 / 116, 6.7 (U = 64)
-      // 481 / 374 / 294, 5.4 (U = 16) 173 / 97 / 78; 26 (U = 32) 79 / 78 / 82, where the
-      // longer sums per wave are not worth it.
+      // (one workgroup of 16 fits): with many centers, fewer waves for fewer
+      // slabs per center.  E / N says nothing of a few long segments, over which
+      // few waves take up to 2.8 times as long, so these wait for a second launch
+      // (tp_backward_long_kernel, 3 us also when there are none); where the rest
+      // gains less than that, 16 waves stay.  Inference backward, 16 waves / few
+      // and the second launch, us, lmax 2 and full parity unless said: 6 slabs,
+      // U = 64, 700 centers 25 / 21, 4,200 124 / 76; 13 slabs, U = 64, 2,100
+      // 90 / 82, 12,000 499 / 393; U = 128 561 / 395; lmax 1 2,100 35.4 / 39.7,
+      // 12,000 187 / 175; 22 slabs, U = 64, 1,100 75.6 / 78.3, 12,000 699 / 643,
+      // lmax 1 4,200 102 / 105.  From 24 on only the wide or narrow ones would
+      // still gain (26 slabs, 16 / 8 waves: U = 64 149 / 144, U = 128 162 / 149,
+      // natural parity 192 / 157, lmax 1 U = 64 132 / 135).
+      // 1,000 edges of one center among 1,100 short ones (U = 64): 16 waves 286,
+      // 4 waves alone 746, with the second launch 298.
       const int64_t N = grid.x, slabs = E * U / kWave;
-      if (N >= kFewCenters && slabs < 16 * N) launch(std::integral_constant<int, 4>{});
-      else if (N >= kFewCenters && slabs < 24 * N) launch(std::integral_constant<int, 8>{});
+      const int64_t many = (slabs < 8 * N ? (Core::FULL ? 640 : 1024) : U > kWave ? 1024 : 2048) * (Core::LMAX == 1 ? 2 : 1);
+      if (N >= many && slabs < 16 * N) launch(std::integral_constant<int, 4>{});
+      else if (N >= many && slabs < 24 * N) launch(std::integral_constant<int, 8>{});
       else launch(std::integral_constant<int, 16>{});
     } else {
       launch(std::integral_constant<int, NW>{});

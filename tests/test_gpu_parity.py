@@ -758,3 +758,38 @@ def test_calls_over_a_range_of_centers_leave_the_other_edges_alone(at, lmax, ful
     gpu = (env.cpu().numpy(), out[:E].cpu().numpy(),
            tuple((o if o is grads[1] else o[:E]).cpu().numpy() for o in grads))
     _compare(t, gpu, (renv, rout, rgrads), f"center ranges lmax{lmax} U{U}")
+
+
+@pytest.mark.parametrize("lmax,full,U", [(1, False, 16), (1, True, 128), (2, False, 64), (2, True, 16), (2, True, 32),
+                                         (2, True, 64), (2, True, 128)])
+@pytest.mark.parametrize("waves", [4, 8])
+def test_backward_takes_long_segments_among_short_ones(at, lmax, full, U, waves):
+    """A backward launch with few waves a center (few slabs a center on average) leaves long segments to a
+    second launch: lengths at either side of the limit, in every lane and wave that looks for them (one
+    center in 256 each), several for one workgroup, the first and the last center."""
+    n, limit = 17000 if waves == 4 else 4100 if lmax == 1 else 2050, 128 * 64 // U
+    at_ = np.array([0, 1, 7, 255, 256, 256 + 7, 512, 512 + 7, n - 1] + ([] if waves == 8 else [
+        30 * 256, 31 * 256, 31 * 256 + 7, 32 * 256, 63 * 256, 64 * 256, 64 * 256 + 1]))
+    at_.sort()
+    degrees = np.zeros(n, dtype=np.int64)
+    degrees[31::97] = 1 + np.arange(len(degrees[31::97])) % 5
+    degrees[at_] = limit + 1 - (np.arange(len(at_)) % 4 == 1) * 2 + (np.arange(len(at_)) % 4 == 3)
+    row_ptr, x, w, y, pw, g = _synthetic(lmax, full, U, degrees, seed=U + waves)
+    E = int(row_ptr[-1])
+    # 8 waves from a mean of 16 slabs on: rows to spare, which no center has
+    rows = E if waves == 4 else 20 * n * 64 // U
+    _note(f"[gpu] long segments lmax={lmax} full={full} U={U} N={n} E={E} rows={rows}")
+    plan = _plan(at, lmax, U, full)
+    rp, pwd, (xd, wd, yd, gd) = _t(row_ptr), _t(pw), (
+        torch.cat([_t(a), torch.zeros((rows - E,) + a.shape[1:], device=DEV)]) for a in (x, w, y, g))
+    env = at.allegro_env_embed(plan, rp, wd, yd)
+    gx, genv, gw, gy = (a.cpu().numpy() for a in at.allegro_tp_backward(plan, rp, xd, env, pwd, gd, wd, yd))
+    busy = np.flatnonzero(degrees)
+    dense = np.concatenate([[0], np.cumsum(degrees[busy])]).astype(np.int64)
+    t = otp.TensorProduct(lmax, full)
+    renv = otp.env_embed(dense, w, y)
+    rgx, rgenv, rgw, rgy = t.backward(dense, x, renv, pw, g, w, y)
+    assert block_rel_err(gx[:E], rgx, t.x_slices) <= BWD_TOL
+    assert block_rel_err(genv[busy], rgenv, t.env_slices) <= BWD_TOL
+    assert np.count_nonzero(genv) == np.count_nonzero(genv[busy])
+    assert block_rel_err(gw[:E], rgw) <= BWD_TOL and block_rel_err(gy[:E], rgy, t.env_slices) <= BWD_TOL
