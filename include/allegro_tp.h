@@ -122,7 +122,11 @@ int allegro_env_embed(const allegro_tp_plan *plan, int64_t N, int64_t E, const i
                       const float *w, const float *Y, float *env, void *stream);
 
 /* Tensor product forward: out[E][U][d1] from x[E][U][d1], env[N][U][d2] and
- * path weights path_w[P][U] (a scalar per path is passed broadcast over U). */
+ * path weights path_w[P][U] (a scalar per path is passed broadcast over U).
+ * More edges than one launch can take (2^25 waves of 64 or 128 rows) go in
+ * several launches; for tests of that path, a plan created while the
+ * environment variable ALLEGRO_SIMULATE_LAUNCH_LIMIT is set to n takes at most
+ * n waves per launch (rounded up to a multiple of 4). */
 int allegro_tp_forward(const allegro_tp_plan *plan, int64_t N, int64_t E, const int64_t *row_ptr,
                        const float *x, const float *env, const float *path_w, float *out,
                        void *stream);

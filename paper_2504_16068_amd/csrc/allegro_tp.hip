@@ -1910,8 +1910,8 @@ int noalloc_scratch(float **out) {
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 using EnvFn = void (*)(dim3, hipStream_t, int64_t, const int64_t *, const float *, const float *, float *);
-using FwdFn = void (*)(int64_t, int64_t, hipStream_t, const int64_t *, const float *, const float *, const float *,
-                       float *);
+using FwdFn = void (*)(int64_t, int64_t, int64_t, hipStream_t, const int64_t *, const float *, const float *,
+                       const float *, float *);
 using BwdFn = void (*)(dim3, int64_t, hipStream_t, const int64_t *, const float *, const float *, const float *, const float *,
                        const float *, const float *, float *, float *, float *, float *, float *, WaitCfg);
 
@@ -1921,11 +1921,11 @@ void launch_env(dim3 grid, hipStream_t s, int64_t N, const int64_t *rp, const fl
 }
 
 constexpr int64_t kFewMatrixCenters = 160;
-constexpr int64_t kFwdLaunchWaves = int64_t(1) << 25;  // waves of one launch of the direct forward
 
+// max_waves: of one launch, a multiple of kFwdWaves
 template <class Core, int U>
-void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const float *x, const float *env,
-                const float *pw, float *out) {
+void launch_fwd(int64_t max_waves, int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const float *x,
+                const float *env, const float *pw, float *out) {
   using L = Lanes<U>;
   if constexpr (Core::LMAX >= 3) {
     // The per-center matrix pays once its construction is shared by enough
@@ -1943,9 +1943,8 @@ void launch_fwd(int64_t N, int64_t E, hipStream_t s, const int64_t *rp, const fl
   auto launch = [&](auto slabs) {
     constexpr int S = decltype(slabs)::value;
     const int64_t waves = (E + S * L::G - 1) / (S * L::G) * L::CPL;
-    // a launch takes fewer than 2^32 threads
-    for (int64_t w0 = 0; w0 < waves; w0 += kFwdLaunchWaves) {
-      const int64_t n = std::min(waves - w0, kFwdLaunchWaves);
+    for (int64_t w0 = 0; w0 < waves; w0 += max_waves) {
+      const int64_t n = std::min(waves - w0, max_waves);
       hipLaunchKernelGGL((tp_forward_kernel<Core, U, S>), dim3(unsigned((n + kFwdWaves - 1) / kFwdWaves)),
                          dim3(kWave * kFwdWaves), 0, s, N, E, w0, rp, x, env, pw, out);
     }
@@ -2180,6 +2179,14 @@ static bool simulated_alloc_failure(const char *what) {
 // still runs to its end, and a validating plan reports ALLEGRO_E_TIMEOUT.
 static bool simulated_handover_timeout() { return std::getenv("ALLEGRO_SIMULATE_HANDOVER_TIMEOUT") != nullptr; }
 
+// For tests: ALLEGRO_SIMULATE_LAUNCH_LIMIT = n at plan creation makes the direct
+// forward take at most n waves per launch (rounded up to whole workgroups).
+static int64_t forward_launch_waves(int64_t limit) {
+  const char *v = std::getenv("ALLEGRO_SIMULATE_LAUNCH_LIMIT");
+  const long long n = v ? std::atoll(v) : 0;
+  return n > 0 && n < limit ? (int64_t(n) + kFwdWaves - 1) / kFwdWaves * kFwdWaves : limit;
+}
+
 int allegro_tp_plan_create(allegro_tp_plan **plan, int lmax, int U, int flags) {
   if (!plan) return fail(ALLEGRO_E_INVALID, "plan output pointer is NULL");
   *plan = nullptr;
@@ -2194,6 +2201,7 @@ int allegro_tp_plan_create(allegro_tp_plan **plan, int lmax, int U, int flags) {
   p->U = U;
   p->flags = flags;
   if (simulated_handover_timeout()) p->spin_limit = 0;
+  p->forward_waves = forward_launch_waves(p->forward_waves);
   try {
     if (simulated_alloc_failure("table")) throw std::bad_alloc();
     p->table = allegro::build_table(lmax, (flags & ALLEGRO_FULL_PARITY) != 0);
@@ -2286,7 +2294,7 @@ int allegro_tp_forward(const allegro_tp_plan *plan, int64_t N, int64_t E, const 
   if ((plan->flags & ALLEGRO_VALIDATE) && (rc = validate_csr(mp, N, E, row_ptr, s))) return rc;
   const Kernels k = select(plan);
   if (!k.fwd) return fail(ALLEGRO_E_UNSUPPORTED, "no kernel for this plan");
-  k.fwd(N, E, s, row_ptr, x, env, path_w, out);
+  k.fwd(plan->forward_waves, N, E, s, row_ptr, x, env, path_w, out);
   return after_launch("allegro_tp_forward");
 }
 

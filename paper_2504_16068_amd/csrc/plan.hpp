@@ -2,6 +2,7 @@
 #pragma once
 
 #include <cstdarg>
+#include <cstdint>
 #include <cstdio>
 #include <mutex>
 #include <string>
@@ -16,6 +17,9 @@ struct allegro_tp_plan {
   // polls before a wait between the waves of the matrix-core backward gives
   // up (0 only to test that path: every such wait then gives up at once)
   int spin_limit = 1 << 24;
+  // waves of one launch of the direct forward, a multiple of 4 (a launch takes
+  // fewer than 2^32 threads; less only to test the loop over launches)
+  int64_t forward_waves = int64_t(1) << 25;
 };
 
 namespace allegro_internal {

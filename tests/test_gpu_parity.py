@@ -682,8 +682,7 @@ def test_step_replays_in_a_hip_graph(at):
 # ------------------------------------------- launch rules of the direct kernels
 
 @pytest.mark.parametrize("lmax,full,U,n,n_edges", [
-    # 512 centers: 4 waves a center below 16 slabs per center on average, 8 below 24, then 16; the
-    # forward takes two slabs a wave from 8192 slabs on
+    # the forward takes two slabs a wave from 8192 slabs on (the backward 16 waves a center with so few centers)
     (1, False, 64, 512, 8191), (1, False, 64, 512, 8192), (1, False, 64, 512, 12287), (1, False, 64, 512, 12288),
     (1, False, 64, 511, 8193), (2, True, 16, 600, 4097), (2, True, 32, 600, 1203), (2, True, 128, 520, 4097),
     # lmax 3: the forward takes the per-center matrix from 32 edges a center on (12 with full parity) and
@@ -700,6 +699,92 @@ def test_launch_rules_parity(at, lmax, full, U, n, n_edges):
     gpu = _np(_run_gpu(at, _plan(at, lmax, U, full), *data))
     t, *ref = _oracle(lmax, full, *data)
     _compare(t, gpu, ref, f"lmax{lmax} U{U} N{n} E{n_edges}")
+
+
+@pytest.mark.parametrize("lmax,full,U,n_edges", [
+    # two slabs a wave (from 8192 slabs on; U = 16: four edges and up to four centers a slab), the last pair
+    # of slabs and the last slab partly past the end
+    (1, False, 16, 32771), (1, True, 16, 32773), (2, True, 16, 32770), (2, False, 32, 16389), (2, True, 64, 8193),
+    (2, False, 128, 4099),
+    # lmax 3, below the edges per center that take the per-center matrix
+    (3, False, 16, 32771), (3, False, 32, 16387), (3, False, 64, 8195), (3, False, 128, 4099), (3, True, 16, 32769),
+    (3, True, 32, 16385), (3, True, 64, 8195), (3, True, 128, 4099),
+])
+def test_forward_pairs_of_slabs_parity(at, lmax, full, U, n_edges):
+    n = n_edges // 6
+    _note(f"[gpu] pairs of slabs lmax={lmax} full={full} U={U} N={n} E={n_edges}")
+    rng = np.random.default_rng(n_edges + U)
+    degrees = np.bincount(rng.integers(0, n, n_edges), minlength=n)
+    row_ptr, x, w, y, pw, _ = _synthetic(lmax, full, U, degrees, seed=n_edges)
+    plan, rp, xd, pwd = _plan(at, lmax, U, full), _t(row_ptr), _t(x), _t(pw)
+    env = at.allegro_env_embed(plan, rp, _t(w), _t(y))
+    out = at.allegro_tp_forward(plan, rp, xd, env, pwd).cpu().numpy()
+    # the oracle on the segments of every 16th center and of the last ones
+    t = otp.TensorProduct(lmax, full)
+    some = np.unique(np.concatenate([np.arange(0, n, 16), np.arange(n - 20, n)]))
+    edges = np.concatenate([np.arange(row_ptr[c], row_ptr[c + 1]) for c in some])
+    sub = np.concatenate([[0], np.cumsum(degrees[some])]).astype(np.int64)
+    ref = t.forward(sub, x[edges], otp.env_embed(sub, w[edges], y[edges]), pw)
+    assert block_rel_err(out[edges], ref, t.x_slices) <= FWD_TOL
+
+
+@pytest.mark.parametrize("lmax,full,U,n_edges", [(1, False, 16, 1003), (2, True, 32, 611), (2, False, 64, 203),
+                                                 (2, True, 128, 131), (3, True, 128, 131)])
+def test_forward_in_several_launches(at, monkeypatch, lmax, full, U, n_edges):
+    """With the waves of one launch limited (they are 2^25), the forward's later launches continue where the
+    one before ended: bit for bit what one launch gives."""
+    rng = np.random.default_rng(n_edges)
+    degrees = np.bincount(rng.integers(0, 90, n_edges), minlength=90)
+    row_ptr, x, w, y, pw, _ = (_t(a) for a in _synthetic(lmax, full, U, degrees, seed=3))
+    whole = _plan(at, lmax, U, full)
+    env = at.allegro_env_embed(whole, row_ptr, w, y)
+    ref = at.allegro_tp_forward(whole, row_ptr, x, env, pw)
+    for limit in (1, 6, 20):
+        _note(f"[gpu] launches of {limit} waves lmax={lmax} full={full} U={U} E={n_edges}")
+        monkeypatch.setenv("ALLEGRO_SIMULATE_LAUNCH_LIMIT", str(limit))
+        plan = _plan(at, lmax, U, full)
+        monkeypatch.delenv("ALLEGRO_SIMULATE_LAUNCH_LIMIT")
+        out = at.allegro_tp_forward(plan, row_ptr, x, env, pw, out=torch.full_like(x, 7.0))
+        assert torch.equal(out.view(torch.uint8), ref.view(torch.uint8)), limit
+
+
+@pytest.mark.parametrize("lmax,full,U,n,mean", [
+    # the backward with 4, 8 and 16 waves a center: below and from 16 and 24 slabs of 64 rows a center on
+    (2, True, 16, 2050, 63), (2, True, 16, 2050, 65), (2, True, 16, 2050, 97), (2, True, 32, 2050, 33),
+    (2, False, 64, 2050, 17), (2, True, 128, 1030, 7), (2, True, 128, 1030, 9), (1, False, 16, 4100, 66),
+    (1, True, 64, 4100, 15), (1, True, 128, 2050, 9),
+    # with fewer slabs a center fewer centers suffice
+    (2, True, 64, 641, 6), (2, False, 16, 1030, 28), (1, True, 32, 1300, 14),
+])
+def test_backward_wave_counts_parity(at, lmax, full, U, n, mean):
+    _note(f"[gpu] backward waves lmax={lmax} full={full} U={U} N={n} mean={mean}")
+    rng = np.random.default_rng(n + mean)
+    degrees = rng.poisson(mean, n)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n + U)
+    d1, d2, n_paths = workloads.dims(lmax, full)
+    row_ptr = np.concatenate([[0], np.cumsum(degrees)]).astype(np.int64)
+    E = int(row_ptr[-1])
+
+    def normal(*shape):
+        return torch.randn(shape, generator=gen, device=DEV)
+
+    x, w, y, g, pw = normal(E, U, d1), normal(E, U), normal(E, d2), normal(E, U, d1), normal(n_paths, U)
+    plan, rp = _plan(at, lmax, U, full), _t(row_ptr)
+    env = at.allegro_env_embed(plan, rp, w, y)
+    gx, genv, gw, gy = at.allegro_tp_backward(plan, rp, x, env, pw, g, w, y)
+    t = otp.TensorProduct(lmax, full)
+    some = np.unique(np.concatenate([np.arange(0, n, 64), np.arange(n - 8, n)]))
+    edges = np.concatenate([np.arange(row_ptr[c], row_ptr[c + 1]) for c in some])
+    sub = np.concatenate([[0], np.cumsum(degrees[some])]).astype(np.int64)
+    at_ = torch.from_numpy(edges).to(DEV)
+    hx, hw, hy, hg = (a[at_].cpu().numpy() for a in (x, w, y, g))
+    hpw = pw.cpu().numpy()
+    rgx, rgenv, rgw, rgy = t.backward(sub, hx, otp.env_embed(sub, hw, hy), hpw, hg, hw, hy)
+    assert block_rel_err(gx[at_].cpu().numpy(), rgx, t.x_slices) <= BWD_TOL
+    assert block_rel_err(genv.cpu().numpy()[some], rgenv, t.env_slices) <= BWD_TOL
+    assert block_rel_err(gw[at_].cpu().numpy(), rgw) <= BWD_TOL
+    assert block_rel_err(gy[at_].cpu().numpy(), rgy, t.env_slices) <= BWD_TOL
 
 
 @pytest.mark.parametrize("U", [16, 32, 64, 128])
