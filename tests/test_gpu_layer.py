@@ -500,6 +500,118 @@ def test_layer_latent_special_values(at, L, H):
                     + H * 2.0 ** -149)
 
 
+@pytest.mark.parametrize("lmax,full,L,H", [(1, False, 64, 64), (1, False, 64, 128), (1, False, 128, 64),
+                                           (1, False, 128, 128), (1, True, 64, 64), (2, False, 64, 64),
+                                           (2, True, 64, 64), (3, False, 64, 64), (3, True, 64, 64)])
+def test_layer_forward_special_values(at, lmax, full, L, H):
+    """What the split products cannot carry (infinities, NaN, values whose products leave their range) goes
+    through the forward's mixing and both products of the latent update as through fp32 ones: in the columns
+    of h, in those of s, in the second product alone, and in a last tile that is not full."""
+    plan, E, deg = _plan(at, lmax, full), 131, [30, 34, 20, 40, 7]
+    row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(lmax, full, L, H, deg, seed=L + H + lmax)
+    big = np.float32(2.0 ** 90)
+    V[3, 5], V[70, 63, 0], V[130, 0] = V[3, 5] * big, np.float32(2.0 ** 100), V[130, 0] * big
+    V[10, 7, 0], V[40, 0, 1], V[129, 33, 0] = np.inf, np.nan, -np.inf
+    V[20, 9], V[65, 3, 0] = 0.0, 3.4e38
+    prm["A"][9:12] = 0.0  # these columns of h reach the latent update only
+    h[1, 9], h[66, 10], h[128, 11], h[72, 9] = big, -big, 2.0 ** 101, 3.4e38
+    h[100, 20] = np.inf  # through w and env, all of the fourth center
+    prm["B2"][0] *= np.float32(2.0 ** 80)  # weights that take the second product out of range as well
+    wd = {k: _t(v) for k, v in prm.items()}
+    _note(f"[gpu] forward special values lmax={lmax} full={full} L={L} H={H}")
+    h_out, V_out, saved = at.allegro_layer_forward(plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+    T, s = _saved_product(saved, plan, len(deg), E)
+    up = lambda n: (4 * n + 255) // 256 * 256  # noqa: E731
+    a0 = up(E * 64) + up(len(deg) * 64 * plan.d2) + up(E * 64 * plan.d1) + up(E * 64)
+    a = saved[a0:a0 + 4 * E * H].view(torch.float32).reshape(E, H)
+
+    ref, mag = _mixed(plan, wd["Mix"], T, False)
+    _as_fp32_products(V_out, ref, mag, MIX_TOL * mag)
+
+    x, b1, b2 = torch.cat([_t(h), s], 1).double(), wd["B1"].double(), wd["B2"].double()
+    mag = x.abs() @ b1.abs()
+    _as_fp32_products(a, x @ b1, mag, (L + 66) * 2.0 ** -24 * mag)
+
+    ad = a.double()
+    z = ad * torch.sigmoid(ad)
+    mag = z.abs() @ b2.abs()
+    # the products, SiLU to a few roundings (flushed to zero past exp's range), and the sum with h
+    bound = (H + 10) * 2.0 ** -24 * mag + 1e-36 * b2.abs().sum(0) + 2.0 ** -24 * (_t(h).double().abs() + mag)
+    _as_fp32_products(h_out, _t(h).double() + z @ b2, mag + _t(h).double().abs(), bound)
+
+
+def _as_fp32_products(got, ref, mag, bound):
+    """got where ref is finite, infinite or NaN, and within the bound of it; sums of terms so large that a
+    partial one may or may not overflow are left out."""
+    sure = ~((mag > 3.0e38) & (mag < float("inf")))
+    r32 = ref.float()
+    assert torch.equal(torch.isnan(got)[sure], torch.isnan(r32)[sure])
+    inf = torch.isinf(r32) & sure
+    assert torch.equal(torch.isinf(got)[sure], torch.isinf(r32)[sure]) and torch.equal(got[inf], r32[inf])
+    ok = torch.isfinite(r32) & sure
+    assert int(ok.sum()) > ok.numel() // 4 and int((mag[ok] > 2.0 ** 84).sum()) > 0
+    assert bool(((got - ref).abs() <= bound)[ok].all())
+
+
+def _cut_to_16_bits(t):
+    """t without the third bf16 part of the split products."""
+    hi = t.bfloat16().float()
+    return hi + (t - hi).bfloat16().float()
+
+
+@pytest.mark.parametrize("lmax,full,L,H", [(1, True, 64, 64), (2, True, 64, 128), (3, False, 128, 64),
+                                           (3, True, 128, 128)])
+def test_layer_products_keep_24_bits(at, lmax, full, L, H):
+    """The root mean square error of every split product, against its own inputs in 64 bits: a sum of n
+    products has n roundings of partial sums no larger than the result, each at most 2^-24 and independent,
+    so sqrt(n) 2^-24 of the result.  Operands of 16 bits would miss it: the same product of cut inputs does."""
+    plan, E = _plan(at, lmax, full), 2003
+    deg = np.full(E // 40 + 1, 40)
+    deg[-1] -= deg.sum() - E
+    row_ptr, h, V, Y, prm, dh_out, dV_out = _synthetic(lmax, full, L, H, deg, seed=7 * L + H)
+    wd = {k: _t(v) for k, v in prm.items()}
+    args = (plan, L, H, _t(row_ptr), _t(h), _t(V), _t(Y), wd)
+    h_out, V_out, saved = at.allegro_layer_forward(*args)
+    work = torch.empty(at.allegro_layer_buffers(plan, L, H, len(deg), E)[1], dtype=torch.uint8, device=DEV)
+    at.allegro_layer_backward(*args, saved, _t(dh_out), _t(dV_out), workspace=work)
+    up = lambda n: (4 * n + 255) // 256 * 256  # noqa: E731
+    T, s = _saved_product(saved, plan, len(deg), E)
+    a0 = up(E * 64) + up(len(deg) * 64 * plan.d2) + up(E * 64 * plan.d1) + up(E * 64)
+    a = saved[a0:a0 + 4 * E * H].view(torch.float32).reshape(E, H)
+    d0 = up(E * 64 * plan.d1)
+    da = work[d0:d0 + 4 * E * H].view(torch.float32).reshape(E, H)
+    s0 = d0 + up(E * H) + up(E * L)
+    ds = work[s0:s0 + 4 * E * 64].view(torch.float32).reshape(E, 64)
+    dT = work[:4 * E * 64 * plan.d1].view(torch.float32).reshape(E, 64, plan.d1)
+
+    def rms(t):
+        return float(t.double().square().mean().sqrt())
+
+    def check(name, got, product, x, w, terms, extra=0.0):
+        ref, cut = product(x, w), product(_cut_to_16_bits(x), _cut_to_16_bits(w))
+        bound = (terms ** 0.5 + extra) * 2.0 ** -24
+        err, lost = rms(got - ref) / rms(ref), rms(cut - ref) / rms(ref)
+        _note(f"  {name}: {err:.2e} of {bound:.2e}, with 16-bit operands {lost:.2e}")
+        assert err <= bound < lost, name
+
+    _note(f"[gpu] 24-bit products lmax={lmax} full={full} L={L} H={H}")
+    dot = lambda x, w: x.double() @ w.double()  # noqa: E731
+    check("V'", V_out, lambda x, w: _mixed(plan, w, x, False)[0], T, wd["Mix"], 64)
+    # dT also has ds on its first component, one more rounding
+    back = lambda x, w: _mixed(plan, w, x, True)[0]  # noqa: E731
+    dT = dT.double()
+    dT[:, :, 0] -= ds.double()
+    check("dT", dT, back, _t(dV_out), wd["Mix"], 64, 1.0)
+    check("a", a, dot, torch.cat([_t(h), s], 1), wd["B1"], L + 64)
+    z = (a.double() * torch.sigmoid(a.double())).float()
+    # SiLU is off by a few roundings, h' by one of the sum with h (left out of the product's size)
+    check("h'", h_out.double() - _t(h).double(), dot, z, wd["B2"], H, 4.0 + rms(_t(h)) / rms(h_out.double() - _t(h).double()))
+    sg = torch.sigmoid(a.double())
+    slope = sg * (1 + a.double() * (1 - sg))
+    check("da", da, lambda x, w: (x.double() @ w.double().t().contiguous()) * slope, _t(dh_out), wd["B2"], L, 4.0)
+    check("ds", ds, lambda x, w: x.double() @ w.double()[L:].t().contiguous(), da, wd["B1"], H)
+
+
 def _same_or_within(got, ref, bound):
     r32 = ref.float()
     # next to the largest float either side of the overflow is within the bound
