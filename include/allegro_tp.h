@@ -43,6 +43,10 @@
  *   fully overwritten (never accumulated) and must not alias any input or each
  *   other.  The library never allocates or frees caller memory and allocates
  *   nothing per call; a plan owns at most a 4-byte device status word.
+ *   Without ALLEGRO_VALIDATE the tensor-product and embedding calls also take
+ *   a range of centers (row_ptr + a with N = b - a, the center tensors from
+ *   center a on, the whole edge tensors with their E) and edge tensors with
+ *   rows to spare: the edge rows of other centers, or of none, are left alone.
  *
  * Execution
  *   Calls are asynchronous on `stream` (a hipStream_t; NULL = the default

@@ -78,7 +78,9 @@ struct XIrreps {
 };
 
 // ------------------------------------------------------ split products
-// fp32 products on the bf16 matrix cores.  x = h + m + l with h = bf16(x),
+// fp32 products on the bf16 matrix cores (the three-way split of G. Henry, P. T.
+// P. Tang, A. Heinecke, "Leveraging the bfloat16 artificial intelligence datatype
+// for higher-precision computations", ARITH 2019).  x = h + m + l with h = bf16(x),
 // m = bf16(x - h), l = x - h - m: 8 significant bits each, rounded to nearest,
 // so the three hold all 24 bits of x exactly (both subtractions are exact).
 // Of the nine products of two split operands the six of weight 2^-16 and more
@@ -314,8 +316,9 @@ struct ChainWeights {
 };
 
 // The three bf16 parts of a [64][K] tile in LDS: part q of row r, column k at
-// (q 64 + r) (K + 8) + k.  The row stride, 4 (mod 64) words, puts the 16-byte
-// operand reads of 16 consecutive rows in distinct banks.
+// (q 64 + r) (K + 8) + k.  The row stride, 36, 68 and 100 words at K = 64, 128
+// and 192, is 4 (mod 32): the 16-byte operand reads of 16 consecutive rows start
+// in 16 distinct quads of banks.
 template <int K>
 struct ChainPlanes {
   static constexpr int STRIDE = K + 8, HALFS = 3 * 64 * STRIDE;  // HALFS: 16-bit elements
@@ -1327,7 +1330,7 @@ DenseTable select_dense(int L, int H) {
 // Launchers of the mixing kernels of one (lmax, parity).
 template <int LMAX, bool FULL>
 struct MixOps {
-  // one workgroup per tile slot the GPU holds at once: each streams a fixed tile sequence
+  // one workgroup per tile slot the GPU holds at once
   template <bool BWD>
   static unsigned grid(int64_t E) {
     static const int64_t slots = resident_groups(reinterpret_cast<const void *>(&mix_kernel<LMAX, FULL, BWD>),

@@ -423,8 +423,8 @@ struct SlabRegs {
 // centers, U = 64), this 1.69; at 6.7 edges per center, where most of those
 // waves had nothing to do, 233 -> 160 us for 100,000 edges; 1,000 centers at
 // U = 32, 48 -> 44 us.
-// Few slabs (under 16 per compute unit with two a wave) go one to a wave:
-// 1,139 edges at U = 16, 4.0 -> 3.3 us.
+// Where two a wave would leave fewer than 16 waves to a compute unit (of the
+// MI355X's 256), slabs go one to a wave: 1,139 edges at U = 16, 4.0 -> 3.3 us.
 constexpr int kFwdWaves = 4;
 constexpr int64_t kFwdPairSlabs = 256 * 16 * 2;  // slabs from which a wave takes two
 
@@ -1930,10 +1930,16 @@ void launch_fwd(int64_t max_waves, int64_t N, int64_t E, hipStream_t s, const in
   if constexpr (Core::LMAX >= 3) {
     // The per-center matrix pays once its construction is shared by enough
     // edges, and needs a center per compute unit; else the edge list is taken
-    // flat.  Matrix / flat, us: natural parity, 11 edges a center (U = 32) 42 /
-    // 34, 20 (U = 32) 59 / 54, 50 (U = 64) 128 / 132; full parity (U = 64), 7.5
-    // edges 468 / 416, 20 edges 274 / 287; 100 centers of 37 edges 34 / 23, 150
-    // of 50 46 / 41, 250 of 50 53 / 65.
+    // flat.  Matrix / flat, us, full parity, 1,000 centers of 9, 20 and 50 edges:
+    // U = 16 20 / 14, 27 / 22, 54 / 61; U = 32 28 / 26, 45 / 45, 95 / 109; U = 64
+    // 43 / 44, 76 / 83, 175 / 206; U = 128 88 / 77, 153 / 159, 340 / 388; 150
+    // centers of 50 edges (U = 64) 42 / 39, 250 50 / 60.  Natural parity, 20 and
+    // 50 edges: U = 16 14 / 9, 24 / 25; U = 32 21 / 18, 44 / 44; U = 64 37 / 35,
+    // 87 / 80; U = 128 73 / 68, 177 / 159.  So the lines fit U = 32 and 64 with
+    // full parity; at U = 16 flat is faster up to 32 edges, and without full
+    // parity the matrix is nowhere much the faster.  Uneven segments favour flat,
+    // which splits them: one center of 4,000 edges among 1,000 of 8 (full
+    // parity, U = 64) 2,275 / 57.
     if (E >= (Core::FULL ? 12 : 32) * N && N >= kFewMatrixCenters) {
       hipLaunchKernelGGL((tp_matrix_kernel<Core, U, TPMFwd<Core::LMAX, Core::FULL>>), dim3(unsigned(N)),
                          dim3(kMFwdThreads<Core>), 0, s, rp, x, env, pw, out);
