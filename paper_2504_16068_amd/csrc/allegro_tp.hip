@@ -2001,10 +2001,12 @@ int64_t mfma_pw_rounds(int64_t N) {
   return int64_t(mfma_grid<FULL, U, true>(N)) * MfmaShape<FULL>::NW / (U / MfmaShape<FULL>::CPW);
 }
 
-// Slabs from which a center waits for tp_backward_long_kernel: with 48, graphs of many
-// such centers (1,100 centers, 80% empty, the others 50 edges at U = 64) took 124 us instead of 72,
-// since that kernel's share-out is fixed; with 128 a center costs at most 0.1 ms of tail.
-constexpr int kLongSlabs = 128;
+// Edges above which a center waits for tp_backward_long_kernel: more than an
+// atom has within the cutoffs in use, or uniform segments short enough for few
+// waves reach.  Where many centers were over the limit that kernel, whose
+// share-out is fixed, took longer than few waves (1,100 centers, 80% empty, the
+// others 50 edges, U = 64: 124 us with a limit of 48 edges, 72 below it).
+constexpr int64_t long_segment(int U) { return U < 32 ? 192 : 128; }
 constexpr unsigned kLongGroups = 256;  // workgroups of that kernel
 
 template <class Core, int U, bool WG>
@@ -2023,7 +2025,7 @@ void launch_bwd(dim3 grid, int64_t E, hipStream_t s, const int64_t *rp, const fl
   } else {
     auto launch = [&](auto waves) {
       constexpr int NW = decltype(waves)::value;
-      const int64_t long_edges = kLongSlabs * kWave / U;
+      constexpr int64_t long_edges = long_segment(U);
       hipLaunchKernelGGL((tp_backward_kernel<Core, U, WG, NW>), grid, dim3(kWave * NW), 0, s, long_edges, rp, x, env, pw,
                          g, w, Y, gx, genv, gw, gy, pw_part);
       if constexpr (NW < TPWaves<Core, U>::bwd(WG))

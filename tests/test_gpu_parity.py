@@ -852,7 +852,7 @@ def test_backward_takes_long_segments_among_short_ones(at, lmax, full, U, waves)
     """A backward launch with few waves a center (few slabs a center on average) leaves long segments to a
     second launch: lengths at either side of the limit, in every lane and wave that looks for them (one
     center in 256 each), several for one workgroup, the first and the last center."""
-    n, limit = 17000 if waves == 4 else 4100 if lmax == 1 else 2050, 128 * 64 // U
+    n, limit = 17000 if waves == 4 else 4100 if lmax == 1 else 2050, 192 if U < 32 else 128  # edges
     at_ = np.array([0, 1, 7, 255, 256, 256 + 7, 512, 512 + 7, n - 1] + ([] if waves == 8 else [
         30 * 256, 31 * 256, 31 * 256 + 7, 32 * 256, 63 * 256, 64 * 256, 64 * 256 + 1]))
     at_.sort()
