@@ -947,8 +947,8 @@ struct BwdLds {
 // pw_part[n][p][u] (the first of the two reduction stages).
 template <class Core, int U, bool WG, int NW>
 __device__ __forceinline__ void backward_center(
-        int wave, int lane, int64_t n, int64_t e0, int64_t e1, float4 *smem, const float *__restrict__ x, const float *__restrict__ env,
-        const float *__restrict__ path_w, const float *__restrict__ g, const float *__restrict__ w,
+        int wave, int lane, int64_t n, int64_t e0, int64_t e1, float4 *smem, const float *__restrict__ x,
+        const float *__restrict__ env, const float *__restrict__ path_w, const float *__restrict__ g, const float *__restrict__ w,
         const float *__restrict__ Y, float *__restrict__ grad_x, float *__restrict__ grad_env,
         float *__restrict__ grad_w, float *__restrict__ grad_Y, float *__restrict__ pw_part) {
   using L = Lanes<U>;
@@ -1032,8 +1032,8 @@ __global__ __launch_bounds__(kWave * NW) __attribute__((amdgpu_waves_per_eu(Kern
   if constexpr (NW < TPWaves<Core, U>::bwd(WG)) {
     if (e1 - e0 > long_edges) return;
   }
-  backward_center<Core, U, WG, NW>(threadIdx.x / kWave, threadIdx.x % kWave, n, e0, e1, smem, x, env, path_w, g, w, Y, grad_x, grad_env, grad_w, grad_Y,
-                                   pw_part);
+  backward_center<Core, U, WG, NW>(threadIdx.x / kWave, threadIdx.x % kWave, n, e0, e1, smem, x, env, path_w, g, w, Y,
+                                   grad_x, grad_env, grad_w, grad_Y, pw_part);
 }
 
 // The centers of more than long_edges edges that a launch with fewer waves per

@@ -605,7 +605,8 @@ def test_layer_products_keep_24_bits(at, lmax, full, L, H):
     check("a", a, dot, torch.cat([_t(h), s], 1), wd["B1"], L + 64)
     z = (a.double() * torch.sigmoid(a.double())).float()
     # SiLU is off by a few roundings, h' by one of the sum with h (left out of the product's size)
-    check("h'", h_out.double() - _t(h).double(), dot, z, wd["B2"], H, 4.0 + rms(_t(h)) / rms(h_out.double() - _t(h).double()))
+    zb = h_out.double() - _t(h).double()
+    check("h'", zb, dot, z, wd["B2"], H, 4.0 + rms(_t(h)) / rms(zb))
     sg = torch.sigmoid(a.double())
     slope = sg * (1 + a.double() * (1 - sg))
     check("da", da, lambda x, w: (x.double() @ w.double().t().contiguous()) * slope, _t(dh_out), wd["B2"], L, 4.0)

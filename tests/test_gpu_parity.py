@@ -826,23 +826,33 @@ def test_calls_over_a_range_of_centers_leave_the_other_edges_alone(at, lmax, ful
     xd, wd, yd, gd = (padded(a, np.nan) for a in (x, w, y, g))
     out = torch.full_like(xd, 7.0)
     env = torch.empty((len(degrees), U, plan.d2), device=DEV)
-    grads = [torch.full_like(xd, 7.0), torch.empty_like(env), torch.full_like(wd, 7.0), torch.full_like(yd, 7.0)]
+    grads = [[torch.full_like(xd, 7.0), torch.empty_like(env), torch.full_like(wd, 7.0), torch.full_like(yd, 7.0)]
+             for _ in range(3)]
+    path_sums = [torch.zeros_like(pwd) for _ in range(3)]
     done = 0
     for a, b in ((0, 4), (4, 5), (5, 8), (8, 14)):
         sub = rp[a:b + 1].clone()
         env[a:b] = at.allegro_env_embed(plan, sub, wd, yd)
         at.allegro_tp_forward(plan, sub, xd, env[a:b].clone(), pwd, out=out)
-        genv = torch.empty((b - a, U, plan.d2), device=DEV)
-        at.allegro_tp_backward(plan, sub, xd, env[a:b].clone(), pwd, gd, wd, yd,
-                               outs=(grads[0], genv, grads[2], grads[3]))
-        grads[1][a:b] = genv
         done = int(row_ptr[b])
-        for o in (out, grads[0], grads[2], grads[3]):
-            assert bool((o[done:] == 7.0).all()), (a, b)
+        args = (plan, sub, xd, env[a:b].clone(), pwd, gd, wd, yd)
+        for k, call in enumerate((at.allegro_tp_backward, at.allegro_tp_backward_train,
+                                  at.allegro_tp_backward_train_noalloc)):
+            genv, gpw = torch.empty((b - a, U, plan.d2), device=DEV), torch.empty_like(pwd)
+            o = grads[k]
+            call(*args, outs=(o[0], genv, o[2], o[3]) + ((gpw,) if k else ()))
+            o[1][a:b] = genv
+            path_sums[k] += gpw if k else 0.0
+            for rows in (out, o[0], o[2], o[3]):
+                assert bool((rows[done:] == 7.0).all()), (a, b, k)
     assert done == E
-    gpu = (env.cpu().numpy(), out[:E].cpu().numpy(),
-           tuple((o if o is grads[1] else o[:E]).cpu().numpy() for o in grads))
-    _compare(t, gpu, (renv, rout, rgrads), f"center ranges lmax{lmax} U{U}")
+    for k in range(3):
+        gpu = (env.cpu().numpy(), out[:E].cpu().numpy(),
+               tuple((o if i == 1 else o[:E]).cpu().numpy() for i, o in enumerate(grads[k])))
+        _compare(t, gpu, (renv, rout, rgrads), f"center ranges lmax{lmax} U{U} call {k}")
+        if k:
+            ref = t.path_weight_grad(row_ptr, x, renv, g)
+            assert block_rel_err(path_sums[k].cpu().numpy(), ref) <= BWD_TOL
 
 
 @pytest.mark.parametrize("lmax,full,U", [(1, False, 16), (1, True, 128), (2, False, 64), (2, True, 16), (2, True, 32),
